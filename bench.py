@@ -38,10 +38,10 @@ HBM_PEAK_GBS = 8000.0
 # timing classes of the library's profiling hook (include/wisp.h) and the kernels they cover
 KERNEL_CLASSES = ((0, "gemm_ring1"), (1, "gemm_ring2"), (2, "gemm_tiled"), (3, "attention"),
                   (4, "attention_combine"), (5, "rows"), (6, "sampler"), (7, "gemm_tile"))
-KERNEL_NAMES = {"gemm_ring1": "gemm_ring_kernel<2, 4, MT/2, 1, 8, 2> (M > 128) / <1, 4, MT, 1, 8, 1>", "gemm_ring2": "gemm_ring_kernel<1, 4, MT, 2, 4, 2>",
+KERNEL_NAMES = {"gemm_ring1": "gemm_ring_kernel<1, 4, MT, 1, 8, 1>", "gemm_ring2": "gemm_ring_kernel<1, 4, MT, 2, 4, 2>",
                 "gemm_tiled": "gemm_f32_kernel", "attention": "attn_bf16_kernel",
                 "attention_combine": "attn_combine_kernel", "rows": "row kernels", "sampler": "sampler kernels",
-                "gemm_tile": "gemm_tile_kernel (LDS-staged output tiles)"}
+                "gemm_tile": "gemm_tile_kernel / gemm_wave_kernel (LDS-staged output tiles)"}
 # algorithmic bytes behind every GB/s figure (the library's profiling hook counts these)
 BYTES_DEFINITION = ("GEMM classes: bf16 weights read once (2 N K per projection); attention: the K and V "
                     "bytes of every cached and new token per kv head; sampler: two fp32 passes over the "

@@ -271,14 +271,14 @@ wisp_status wisp_check(void *workspace, void *stream);
  * process: enable, read and reset it from one thread, while no other thread calls the
  * library.
  */
-#define WISP_PROF_GEMM_RING1 0   /* gemm_ring_kernel, one 32-column fragment per wave (4 or 8 waves) */
+#define WISP_PROF_GEMM_RING1 0   /* gemm_ring_kernel, one 32-column fragment per wave */
 #define WISP_PROF_GEMM_RING2 1   /* gemm_ring_kernel, two 32-column fragments per wave  */
 #define WISP_PROF_GEMM_TILED 2   /* the fp32 GEMM                                        */
 #define WISP_PROF_ATTN 3         /* attn_bf16_kernel / attn_f32_kernel                   */
 #define WISP_PROF_ATTN_COMBINE 4 /* attn_combine_kernel                                  */
 #define WISP_PROF_ROWS 5         /* embedding, norms, RoPE + KV append, SwiGLU           */
 #define WISP_PROF_SAMPLER 6      /* acceptance kernels                                    */
-#define WISP_PROF_GEMM_TILE 7    /* gemm_tile_kernel, LDS-staged output tiles (>= 161 rows) */
+#define WISP_PROF_GEMM_TILE 7    /* gemm_tile_kernel, gemm_wave_kernel: LDS-staged output tiles */
 #define WISP_PROF_KINDS 8
 wisp_status wisp_profile_enable(int on);
 wisp_status wisp_profile_read(int kind, double *ms, int64_t *launches, double *bytes, double *flops);
@@ -287,11 +287,10 @@ wisp_status wisp_profile_reset(void);
 /*
  * Launch plan of one bf16 projection of the step (host only; introspection for tests and
  * benchmarks): M rows, N output columns, K inputs.  out[0] = kernel variant (1: 32-column
- * weight ring, 2: 64-column weight ring, 3: 32-column weight ring with two waves per SIMD,
- * 4: LDS-staged output tiles, from 161 rows), out[1] = row blocks (row tiles),
- * out[2] = 32-row fragments per row block, out[3] = K ranges whose fp32 partial sums are
- * added in fixed order.  WISP_E_INVALID for M, N or K < 1, or N and
- * K not multiples of 32 and 16.
+ * weight ring, 2: 64-column weight ring, 4: LDS-staged output tiles), out[1] = row blocks,
+ * out[2] = 32-row fragments per row block (a block of 12 is two row tiles of 192 rows, any
+ * other block one row tile), out[3] = K ranges whose fp32 partial sums are added in fixed
+ * order.  WISP_E_INVALID for M, N or K < 1, or N and K not multiples of 32 and 16.
  */
 wisp_status wisp_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t out[4]);
 

@@ -2,12 +2,13 @@
 //
 // bf16 path: both operands are pre-packed into 32x16 fragments (lane order of gfx950's
 // v_mfma_f32_32x32x16_bf16), so each wave-level load of a fragment is one contiguous
-// 1 KiB read.  Every workgroup holds the activations of a block of at most 256 rows
-// (staged through double-buffered LDS) while each wave streams its own weight fragments
-// straight into a register ring, accumulating in fp32.  The verify step's sum(gamma+1)
-// rows make these shapes HBM-bound on the weight stream up to about 315 rows; K is split
-// across workgroups when there are too few output tiles to fill the 256 CUs, and the
-// fp32 partial sums are added in a fixed order by the consuming epilogue kernel.
+// 1 KiB read.  The ring kernel here serves small row counts (at most 160): every workgroup
+// holds the activations of all rows (staged through double-buffered LDS) while each wave
+// streams its own weight fragments straight into a register ring, accumulating in fp32.
+// The verify step's sum(gamma+1) rows make these shapes HBM-bound on the weight stream up
+// to about 315 rows; K is split across workgroups when there are too few output tiles to
+// fill the 256 CUs, and the fp32 partial sums are added in a fixed order by the consuming
+// epilogue kernel.  Larger row counts take the tiles of gemm_tile.hip.
 #include <type_traits>
 
 #include "common.h"
@@ -210,93 +211,107 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_ring_kernel(const uint16_t 
 }
 
 static constexpr int kNarrowAD = 1;   // activation prefetch depth of the 32-column ring
-// From this many 32-row fragments on, the 32-column ring runs 8 waves per workgroup (two per
-// SIMD, each on half of the rows), so one wave's products issue while the other waits for
-// memory; below it the extra zero rows and doubled weight requests cost more than that buys
-static constexpr int kPairedWavesMinMT = 5;
 
 // Launch plan.  LDS-staged output tiles (gemm_tile.hip) for most shapes, the weight ring
-// (above) where it streams faster or K does not fit the tile's chunk.  Tile variant by
-// row fragments, measured with cold weights on the 8B and 70B projections at 7-1237 rows:
+// (above) where it streams faster or K does not fit the tile's chunks (at most 64 rows and K
+// not a multiple of 64).  Tile variant by
+// row fragments, measured with cold weights on the 8B and 70B projections at 7-4108 rows:
 //   1 (<= 32 rows): the 32 x 256 tile with up to 16 K splits for projections of >= 20M
 //     weights (at 7 rows QKV 13.4 -> 11.5 us, down 24.0 -> 20.1, LM head 169.5 -> 158.9);
 //     the output projection streams as fast on the ring; outputs of 16384-32768 columns
 //     (the 8B gate/up) take 64 x 128 tiles in one K range, which fill as many CUs as the
 //     32-row tile with two (at 7-23 rows 36-39 us against 38-40) and keep the SwiGLU
 //     epilogue (8B steps at B = 1, 2, 4: 4.05 -> 3.84, 4.12 -> 3.90, 4.38 -> 4.12 ms);
-//   2: 64 x 128 tiles, 3-4: 128 x 128 (10-23 % faster than the ring on QKV, O, gate/up
-//     and down); the LM head stays on the ring (the tiles 7-44 % slower for it at 41-150
-//     rows);
-//   5: the 192-row tile (QKV 22.1 -> 19.5 us, down 38.4 -> 32.4; gate/up in one K range
-//     as fast as the ring with two, 59.0 against 60.5 us, and with the SwiGLU epilogue:
-//     8B steps at B = 26 / 28 6.89 / 6.93 -> 6.74 / 6.79 ms);
-//     the ring for the LM head;
-//   6: 192-row tiles, 256 columns wide only for the LM head (measured over whole steps: for
-//     gate/up the 128-column tile in one K range, with the SwiGLU epilogue, beats the
-//     256-column one, which needs two K ranges to fill the CUs);
-//   7-8: one 256-row tile, 256 columns wide for the LM head (at 240 rows 374 -> 325 us);
-//     at 128 columns for the rest (gate/up keeps one K range and its SwiGLU epilogue);
-//   9-12: one 384-row tile (at 343-370 rows 10-25 % faster than two 256-row tiles);
-//   beyond (> 384 rows): 256 x 256 tiles with the K split below (at 476-1237 rows 9-30 %
-//     off QKV + O + down per layer against 384- or 256-row tiles of 128 columns: 8B at
-//     1237 rows 371 -> 259 us, 70B at 476 rows 512 -> 380 us; in the 8B step at 1237 rows
-//     the projections 21.9 -> 19.3 ms, the row kernels reading the added partials
-//     1.87 -> 2.61 ms, the step 45.5 -> 44.2 ms).
+//   2: 64 x 128 tiles; the LM head stays on the ring up to 160 rows;
+//   3-4, 5-6, 7-8: one tile of 128, 192 or 256 rows (a row tile that holds every row lets the
+//     weights stream past the caches), 128 columns wide; 256 columns wide where those tiles
+//     alone fill a round of the 256 CUs (>= kWideTiles: the 70B gate/up, the LM heads), since
+//     they read the activations half as often: 70B gate/up at 128 rows 198 -> 146 us, at 171
+//     rows 243 -> 184 us (128 columns: 210), the 8B LM head at 171 rows 257 -> 230 us;
+//   9-12: one row block of 384 rows as two 192 x 256 tiles side by side (70B at 370 rows:
+//     gate/up 384 -> 320 us against a 384 x 128 tile, 347 us in this kernel);
+//   beyond (> 384 rows): 256 x 256 tiles, or 192 x 256 where kTileUs estimates at least an
+//     eighth less time: fewer padded rows or fuller rounds (8B at 1291 rows: QKV 87 -> 74,
+//     down 137 -> 122 us); closer calls go either way by a few percent and stay at 256.
 // K is split into as many ranges as the work items fit one round of 256 workgroups (at
-// most 8, 16 for the 32-row tile), each range keeping at least 8 chunks: not only powers
-// of two, since a round that leaves CUs idle costs the GEMM more than the row kernels save
-// on fewer partials (QKV of 80 tiles on 3 ranges: 70B at 370 rows 92 -> 72 us alone, the
-// 70B step 76.9 -> 75.8 ms; QKV of 48 tiles on 5: 8B at 100 rows 16.5 -> 14.9 us alone, the
-// 8B step at 171 rows unchanged, the extra partial costing the row kernels what it saves).
-// The ring holds all rows of a row block of at most 256 rows: 64-column wave tiles for
-// wide outputs, 32-column tiles with a deeper ring otherwise (8 waves per workgroup from
-// kPairedWavesMinMT row fragments on); K split for one resident round.
+// most 8, 16 for the 32-row tile), each range keeping at least the variant's min_k columns:
+// not only powers of two, since a round that leaves CUs idle costs the GEMM more than the
+// row kernels save on fewer partials (QKV of 80 tiles on 3 ranges: 70B at 370 rows 92 -> 72
+// us alone, the 70B step 76.9 -> 75.8 ms; QKV of 48 tiles on 5: 8B at 100 rows 16.5 -> 14.9 us
+// alone, the 8B step at 171 rows unchanged, the extra partial costing the row kernels what it
+// saves).
+// The ring holds all rows (at most 160 reach it): 64-column wave tiles for wide outputs,
+// 32-column tiles with a deeper ring otherwise; K split for one resident round.
+static constexpr int kRound = 256;        // workgroups resident at once (one per CU)
+static constexpr int kWideTiles = 224;    // 7/8 of a round
+// measured time of one 32-column chunk of a full round of 256-column tiles, and what a round
+// costs besides (first loads, stores), in microseconds
+struct TileUs { double chunk, round; };
+static constexpr TileUs kTileUs256 = {0.59, 6.0}, kTileUs192 = {0.48, 6.0};
+
+// K ranges of `tiles` output tiles: the count and the chunks of 16 ks columns per range
+static void split_k(int tiles, int K, const TileShape &ts, int s_max, int *splits, int *per_range) {
+  const int KC = K / (16 * ts.ks);
+  int s = std::max(1, std::min(s_max, kRound / tiles));
+  while (s > 1 && KC / s * 16 * ts.ks < ts.min_k) --s;
+  const int kcs = (KC + s - 1) / s;
+  *splits = (KC + kcs - 1) / kcs;
+  *per_range = kcs;
+}
+
+static int tile_count(int mf, int N, const TileShape &ts) {
+  return ((mf * 32 + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
+}
+
 GemmCfg gemm_bf16_plan(int M, int N, int K) {
   GemmCfg c{};
   const int mf = (M + 31) / 32;
   const int KF = K / 16;
   const bool lm_wide = N >= 65536;
+  const bool fills = (N + 255) / 256 >= kWideTiles;
   int variant;
   if (mf == 1) variant = N >= 16384 && N <= 32768 ? 6 : (int64_t)N * K >= ((int64_t)20 << 20) ? 5 : 0;
   else if (mf == 2) variant = lm_wide ? 0 : 6;
-  else if (mf <= 4) variant = lm_wide ? 0 : 7;
-  else if (mf == 5) variant = lm_wide ? 0 : 1;
-  else if (mf == 6) variant = lm_wide ? 4 : 1;
-  else if (mf <= 8) variant = lm_wide ? 17 : 13;
-  else if (mf <= 12) variant = 12;
-  else variant = 17;
+  else if (mf <= 4) variant = lm_wide ? 0 : fills ? 8 : 7;
+  else if (mf == 5) variant = lm_wide ? 0 : fills ? 4 : 1;
+  else if (mf == 6) variant = fills ? 4 : 1;
+  else if (mf <= 8) variant = fills ? 17 : 13;
+  else if (mf <= 12) variant = 4;
+  else {
+    auto us = [&](int v, const TileUs &u) {
+      const TileShape ts = tile_shape(v);
+      const int tiles = tile_count(mf, N, ts);
+      int s, kcs;
+      split_k(tiles, K, ts, 8, &s, &kcs);
+      return (double)((tiles * (int64_t)s + kRound - 1) / kRound) * (kcs * u.chunk + u.round);
+    };
+    variant = us(4, kTileUs192) < 0.875 * us(17, kTileUs256) ? 4 : 17;
+  }
   if (variant) {
     const TileShape ts = tile_shape(variant);
     if (K % (16 * ts.ks) == 0) {
-      const int tiles = ((mf * 32 + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
-      const int KC = K / (16 * ts.ks);
-      const int s_max = variant == 5 ? 16 : 8;
-      int s = std::max(1, std::min(s_max, 256 / tiles));
-      while (s > 1 && KC / s < 8) --s;
-      const int kcs = (KC + s - 1) / s;
+      int s, kcs;
+      split_k(tile_count(mf, N, ts), K, ts, variant == 5 ? 16 : 8, &s, &kcs);
       c.kind = 4;
       c.variant = variant;
       c.bm = ts.bm;
       c.bn = ts.bn;
-      c.mt = ts.bm / 32;
-      c.rb = (mf * 32 + ts.bm - 1) / ts.bm;
-      c.splits = (KC + kcs - 1) / kcs;
+      // 257-384 rows: one row block, the two row tiles of which run side by side
+      c.rb = mf > 8 && mf <= 12 ? 1 : (mf * 32 + ts.bm - 1) / ts.bm;
+      c.mt = mf > 8 && mf <= 12 ? 12 : ts.bm / 32;
+      c.splits = s;
       c.kf_per_split = kcs * ts.ks;
       return c;
     }
   }
-  // rows in rb blocks of at most 8 fragments, balanced; each block is one grid row of
-  // workgroups that stream the same weights (the grid width is a multiple of 8 for every
-  // projection here, so a tile's row blocks share an XCD and its L2)
-  c.rb = (mf + 7) / 8;
-  int mt = (mf + c.rb - 1) / c.rb;
-  c.kind = N >= 16384 ? 2 : (mt >= kPairedWavesMinMT ? 3 : 1);
-  if (c.kind == 3 && c.rb > 1) mt += mt & 1;   // paired halves: a block is 2 * ceil(mt / 2) fragments
-  c.mt = mt;
-  c.bm = 32 * mt;
+  // every row in one block (at most 5 fragments reach the ring)
+  c.rb = 1;
+  c.kind = N >= 16384 ? 2 : 1;
+  c.mt = mf;
+  c.bm = 32 * mf;
   c.bn = c.kind == 2 ? 256 : 128;
   const int R = c.kind == 2 ? 4 : 8;
-  const int tiles = ((N + c.bn - 1) / c.bn) * c.rb;
+  const int tiles = (N + c.bn - 1) / c.bn;
   // workgroups resident at once: the ring kernels hold one workgroup per CU (LDS and
   // registers), so more than one round of 256 would leave a partial second round
   const int max_wg = 256;
@@ -307,15 +322,6 @@ GemmCfg gemm_bf16_plan(int M, int N, int K) {
   c.splits = (KF + kps - 1) / kps;
   c.kf_per_split = kps;
   return c;
-}
-
-// 32-column ring, 8 waves: two row halves of ceil(mt / 2) fragments each
-static void launch_ring_paired(int mt, dim3 grid, const uint16_t *A, const uint16_t *W, float *C, int M,
-                               int N, int K, int ldc, int kps, RowMaxOut rm, hipStream_t s) {
-  switch ((mt + 1) / 2) {
-    case 3: launch(gemm_ring_kernel<2, 4, 3, 1, 8, 2>, grid, 512, 0, s, A, W, C, M, N, K, ldc, kps, rm); break;
-    case 4: launch(gemm_ring_kernel<2, 4, 4, 1, 8, 2>, grid, 512, 0, s, A, W, C, M, N, K, ldc, kps, rm); break;
-  }
 }
 
 template <int NT, int R, int AD>
@@ -329,9 +335,6 @@ static void launch_ring(int mt, dim3 grid, const uint16_t *A, const uint16_t *W,
     WISP_RING_CASE(3)
     WISP_RING_CASE(4)
     WISP_RING_CASE(5)
-    WISP_RING_CASE(6)
-    WISP_RING_CASE(7)
-    WISP_RING_CASE(8)
 #undef WISP_RING_CASE
   }
 }
@@ -345,8 +348,6 @@ void gemm_bf16(const uint16_t *A, const uint16_t *W, float *C, int M, int N, int
   dim3 grid(((N + cfg.bn - 1) / cfg.bn) * cfg.splits, cfg.rb, 1);
   if (cfg.kind == 1)
     launch_ring<1, 8, kNarrowAD>(cfg.mt, grid, A, W, C, M, N, K, ldc, cfg.kf_per_split, rm, s);
-  else if (cfg.kind == 3)
-    launch_ring_paired(cfg.mt, grid, A, W, C, M, N, K, ldc, cfg.kf_per_split, rm, s);
   else
     launch_ring<2, 4, 2>(cfg.mt, grid, A, W, C, M, N, K, ldc, cfg.kf_per_split, rm, s);
 }

@@ -27,7 +27,6 @@ inline void launch(void (*kernel)(Formals...), dim3 grid, dim3 block, uint32_t s
 // ----- GEMMs: C[z][M][ldc] (fp32) = A[M][K] . W[N][K]^T over the z-th K range ----------
 struct GemmCfg {
   int kind;         // 1: weight ring NT=1 R=8, 2: weight ring NT=2 R=4,
-                    // 3: weight ring NT=1 R=8 with 8 waves (two per SIMD on half the rows each),
                     // 4: LDS-staged output tiles (gemm_bf16_tile, `variant`)
   int variant;      // kind 4: tile shape (see gemm_bf16_tile)
   int mt;           // 32-row fragments of A held by every workgroup
@@ -41,12 +40,13 @@ void gemm_bf16(const uint16_t *A_packed, const uint16_t *W_packed, float *C, int
                int ldc, const GemmCfg &cfg, hipStream_t s, RowMaxOut rm = RowMaxOut{nullptr, nullptr, 0},
                SwigluOut sw = SwigluOut{nullptr, 0});
 void gemm_f32(const float *A, const float *W, float *C, int M, int N, int K, int ldc, hipStream_t s);
-// LDS-staged output tiles (both operands staged through LDS): variant 1 is 192 x 128,
-// 4 is 192 x 256, 6 is 64 x 128, 7 is 128 x 128, 12 is 384 x 128, 13 is 256 x 128 and
-// 17 is 256 x 256 (rows x columns, 8 waves), 5 is 32 x 256 (4 waves).  K is
-// cut into chunks of 16 ks (ks = tile_k_steps(variant)); a work item sums kc_split chunks
-// into its own fp32 partial C[z] (z = its K range), C[0] alone when kc_split covers K.
-struct TileShape { int bm, bn, ks; };
+// LDS-staged output tiles (both operands staged through LDS): variant 1 is 192 x 128, 4 is
+// 192 x 256, 7 is 128 x 128, 8 is 128 x 256, 13 is 256 x 128 and 17 is 256 x 256 (rows x
+// columns; 4 waves, one per SIMD), 6 is 64 x 128 (8 waves), 5 is 32 x 256 (4 waves).
+// K is cut into chunks of 16 ks; a work item sums kc_split chunks into its own fp32 partial
+// C[z] (z = its K range), C[0] alone when kc_split covers K.  min_k: the fewest K columns of
+// a range when K is split.
+struct TileShape { int bm, bn, ks, min_k; };
 TileShape tile_shape(int variant);
 void gemm_bf16_tile(const uint16_t *A_packed, const uint16_t *W_packed, float *C, int M, int N, int K, int ldc,
                     int variant, int kc_split, RowMaxOut rm, hipStream_t s, SwigluOut sw = SwigluOut{nullptr, 0});
