@@ -44,7 +44,7 @@ KERNEL_NAMES = {"gemm_ring1": "gemm_ring_kernel<1, 4, MT, 1, 8, 1>", "gemm_ring2
                 "gemm_tile": "gemm_tile_kernel / gemm_wave_kernel (LDS-staged output tiles)"}
 # algorithmic bytes behind every GB/s figure (the library's profiling hook counts these)
 BYTES_DEFINITION = ("GEMM classes: bf16 weights read once (2 N K per projection); attention: the K and V "
-                    "bytes of every cached and new token per kv head; sampler: two fp32 passes over the "
+                    "bytes of every cached and new token per kv head; sampler: one fp32 pass over the "
                     "logits plus one row per request")
 EXTRA_CONFIGS = "8b_b256,8b_dyn128,70b_b64"
 BF16_PEAK_TFLOPS = 2516.6

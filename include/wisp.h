@@ -265,7 +265,7 @@ wisp_status wisp_check(void *workspace, void *stream);
  * the algorithmic bytes / flops of its launches:
  *   GEMM classes: the weights, 2 (bf16) or 4 (fp32) bytes x N*K, read once per step;
  *   ATTN: K and V bytes of every token each kv head reads (ctx_len + gamma + 1 per request);
- *   SAMPLER: two passes over the fp32 logits plus one row per request;
+ *   SAMPLER: one pass over the fp32 logits plus one logits and one q row per request;
  *   ATTN_COMBINE, ROWS: none (overhead kernels).
  * wisp_profile_read synchronises on the recorded events.  The profiling state is one per
  * process: enable, read and reset it from one thread, while no other thread calls the

@@ -53,12 +53,12 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-template <int WGM, int WGN, int MTW, int NTW, int KS, int ST, bool RM, bool SW>
+template <int WGM, int WGN, int MTW, int NTW, int KS, int ST, bool SW>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(const uint16_t *__restrict__ A,
                                                         const uint16_t *__restrict__ W,
                                                         float *__restrict__ C, int M, int N, int K,
                                                         int ldc, int tiles_m, int tiles, int per_xcd,
-                                                        int kc_split, RowMaxOut rmax, SwigluOut sw) {
+                                                        int kc_split, SwigluOut sw) {
   constexpr int NW = WGM * WGN;               // waves
   constexpr int AF = WGM * MTW, BF = WGN * NTW;   // A / W fragments of the tile per K step
   constexpr int SF = (AF + BF) * KS;          // fragments per stage
@@ -245,12 +245,6 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(const uint16_
       }
     }
   }
-  if (RM) {   // LM head: the row maxima of this tile's columns (its own instance: the
-             // maxima need registers that the plain projections spend on their tiles)
-    __syncthreads();   // every wave is done with the stage buffers (no load is in flight)
-    tile_row_max<WGM, WGN, MTW, NTW>(acc, reinterpret_cast<float *>(&lds0[0][0]), nb0 + wn * NTW, NF, N, M,
-                                     rb0 * 32, wm * MTW, wn, tn, rmax);
-  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -274,7 +268,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_tile_kernel(const uint16_
 //    cover a compact block of tiles; see the tile order below.
 // Operands swap places in the product (weights first), so lane l holds row l % 16 and four
 // consecutive columns 4 (l / 16) .. + 3 of each 16 x 16 block: results leave as 16-byte
-// stores, SwiGLU pairs and row maxima stay inside the lane.
+// stores and SwiGLU pairs stay inside the lane.
 //
 // The operand of a 16-row block and 32 K columns is four 256-byte runs of two packed
 // fragments: lane l reads row l % 16, columns 8 (l / 16) .. + 7 (conflict-free).
@@ -314,12 +308,12 @@ constexpr WaveSched wave_sched(int P, int R, int LPW) {
 
 // STREAM: weight loads marked non-temporal, for launches of one row tile (each weight is
 // then read by one workgroup only; with several row tiles it costs 10-15 % because the
-// other tiles' reads miss).  RM: row maxima (LM head), SW: SwiGLU (gate/up).
-template <int WM, int WN, int MT, int NT, bool STREAM, bool RM, bool SW>
+// other tiles' reads miss).  SW: SwiGLU (gate/up).
+template <int WM, int WN, int MT, int NT, bool STREAM, bool SW>
 __global__ __launch_bounds__(256, 1) void gemm_wave_kernel(const uint16_t *__restrict__ A,
                                                            const uint16_t *__restrict__ W, float *__restrict__ C,
                                                            int M, int N, int K, int ldc, int tiles_m, int tiles,
-                                                           int per_xcd, int kc_split, RowMaxOut rmax, SwigluOut sw) {
+                                                           int per_xcd, int kc_split, SwigluOut sw) {
   static_assert(WM * WN == 4, "one wave per SIMD");
   constexpr int ST = kWaveStages;
   constexpr int AF = WM * MT, BF = WN * NT;     // A / W row blocks (32 rows) of the tile
@@ -517,106 +511,45 @@ __global__ __launch_bounds__(256, 1) void gemm_wave_kernel(const uint16_t *__res
       *reinterpret_cast<floatx4 *>(C + (int64_t)row * ldc + nb * 32 + (j & 1) * 16 + 4 * (lane >> 4)) = acc[i][j];
     }
   }
-  if constexpr (RM) {
-    // Row maxima of the tile: a lane scans its row's columns in ascending order per block, the
-    // four lanes of a row combine by value, then smaller column; the waves of a row through LDS
-    // (23 us -> about 1 us per 256 x 256 tile against a butterfly over 32 lanes per element)
-    constexpr int ROWS = AF * 32;
-    float *sh = reinterpret_cast<float *>(lds);
-    int *shc = reinterpret_cast<int *>(lds) + WN * ROWS;
-    __syncthreads();   // every wave has read its last stage
-#pragma unroll
-    for (int i = 0; i < MA; ++i) {
-      float bv = -INFINITY;
-      int bc = 0x7FFFFFFF;
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const int nb = nb0 + wn * NT + (j >> 1);
-        if (nb >= NF) continue;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (acc[i][j][e] > bv) {
-            bv = acc[i][j][e];
-            bc = nb * 32 + (j & 1) * 16 + 4 * (lane >> 4) + e;
-          }
-      }
-#pragma unroll
-      for (int o = 16; o < 64; o <<= 1) {
-        const float ov = __shfl_xor(bv, o);
-        const int oc = __shfl_xor(bc, o);
-        if (ov > bv || (ov == bv && oc < bc)) {
-          bv = ov;
-          bc = oc;
-        }
-      }
-      if (lane < 16) {
-        sh[wn * ROWS + wm * MT * 32 + 16 * i + lane] = bv;
-        shc[wn * ROWS + wm * MT * 32 + 16 * i + lane] = bc;
-      }
-    }
-    __syncthreads();
-    for (int lr = threadIdx.x; lr < ROWS; lr += 256) {
-      const int row = rb0 * 32 + lr;
-      if (row >= M) continue;
-      float bv = sh[lr];
-      int bc = shc[lr];
-      for (int x = 1; x < WN; ++x) {
-        const float ov = sh[x * ROWS + lr];
-        const int oc = shc[x * ROWS + lr];
-        if (ov > bv || (ov == bv && oc < bc)) {
-          bv = ov;
-          bc = oc;
-        }
-      }
-      rmax.m[(int64_t)row * rmax.tiles + tn] = bv;
-      rmax.i[(int64_t)row * rmax.tiles + tn] = bc;
-    }
-  }
 }
 
 template <int WM, int WN, int MT, int NT, bool STREAM>
-static void launch_wave_as(const uint16_t *A, const uint16_t *W, float *C, int M, int N, int K, int ldc, RowMaxOut rm,
-                           hipStream_t s, int kc_split, SwigluOut sw) {
+static void launch_wave_as(const uint16_t *A, const uint16_t *W, float *C, int M, int N, int K, int ldc, hipStream_t s,
+                           int kc_split, SwigluOut sw) {
   const int tiles_m = ((M + 31) / 32 + WM * MT - 1) / (WM * MT);
   const int tiles_n = (N / 32 + WN * NT - 1) / (WN * NT);
   const int splits = (K / 32 + kc_split - 1) / kc_split;
   const int tiles = tiles_m * tiles_n, per_xcd = (tiles * splits + 7) / 8;
   auto go = [&](auto kernel) {
-    launch(kernel, 8 * per_xcd, 256, 0, s, A, W, C, M, N, K, ldc, tiles_m, tiles, per_xcd, kc_split, rm, sw);
+    launch(kernel, 8 * per_xcd, 256, 0, s, A, W, C, M, N, K, ldc, tiles_m, tiles, per_xcd, kc_split, sw);
   };
-  if (rm.m) go(gemm_wave_kernel<WM, WN, MT, NT, STREAM, true, false>);
-  else if (sw.out) go(gemm_wave_kernel<WM, WN, MT, NT, STREAM, false, true>);
-  else go(gemm_wave_kernel<WM, WN, MT, NT, STREAM, false, false>);
+  if (sw.out) go(gemm_wave_kernel<WM, WN, MT, NT, STREAM, true>);
+  else go(gemm_wave_kernel<WM, WN, MT, NT, STREAM, false>);
 }
 
 template <int WM, int WN, int MT, int NT>
-static void launch_wave(const uint16_t *A, const uint16_t *W, float *C, int M, int N, int K, int ldc, RowMaxOut rm,
-                        hipStream_t s, int kc_split, SwigluOut sw) {
+static void launch_wave(const uint16_t *A, const uint16_t *W, float *C, int M, int N, int K, int ldc, hipStream_t s,
+                        int kc_split, SwigluOut sw) {
   if (M <= 32 * WM * MT)
-    launch_wave_as<WM, WN, MT, NT, true>(A, W, C, M, N, K, ldc, rm, s, kc_split, sw);
+    launch_wave_as<WM, WN, MT, NT, true>(A, W, C, M, N, K, ldc, s, kc_split, sw);
   else
-    launch_wave_as<WM, WN, MT, NT, false>(A, W, C, M, N, K, ldc, rm, s, kc_split, sw);
+    launch_wave_as<WM, WN, MT, NT, false>(A, W, C, M, N, K, ldc, s, kc_split, sw);
 }
 
 template <int WGM, int WGN, int MTW, int NTW, int KS, int ST>
 static void launch_tile(const uint16_t *A, const uint16_t *W, float *C, int M, int N, int K, int ldc,
-                        RowMaxOut rm, hipStream_t s, int kc_split, SwigluOut sw) {
-  static_assert(2 * WGN * WGM * MTW * 32 * 4 <= (WGM * MTW + WGN * NTW) * KS * 1024,
-                "the row-maxima exchange fits one stage buffer");
+                        hipStream_t s, int kc_split, SwigluOut sw) {
   const int tiles_m = ((M + 31) / 32 + WGM * MTW - 1) / (WGM * MTW);
   const int tiles_n = (N / 32 + WGN * NTW - 1) / (WGN * NTW);
   const int KC = K / (16 * KS);
   const int splits = (KC + kc_split - 1) / kc_split;
   const int tiles = tiles_m * tiles_n, per_xcd = (tiles * splits + 7) / 8;
-  if (rm.m)
-    launch(gemm_tile_kernel<WGM, WGN, MTW, NTW, KS, ST, true, false>, 8 * per_xcd, 64 * WGM * WGN, 0, s, A, W, C, M,
-           N, K, ldc, tiles_m, tiles, per_xcd, kc_split, rm, sw);
-  else if (sw.out)
-    launch(gemm_tile_kernel<WGM, WGN, MTW, NTW, KS, ST, false, true>, 8 * per_xcd, 64 * WGM * WGN, 0, s, A, W, C, M,
-           N, K, ldc, tiles_m, tiles, per_xcd, kc_split, rm, sw);
+  if (sw.out)
+    launch(gemm_tile_kernel<WGM, WGN, MTW, NTW, KS, ST, true>, 8 * per_xcd, 64 * WGM * WGN, 0, s, A, W, C, M,
+           N, K, ldc, tiles_m, tiles, per_xcd, kc_split, sw);
   else
-    launch(gemm_tile_kernel<WGM, WGN, MTW, NTW, KS, ST, false, false>, 8 * per_xcd, 64 * WGM * WGN, 0, s, A, W, C, M,
-           N, K, ldc, tiles_m, tiles, per_xcd, kc_split, rm, sw);
+    launch(gemm_tile_kernel<WGM, WGN, MTW, NTW, KS, ST, false>, 8 * per_xcd, 64 * WGM * WGN, 0, s, A, W, C, M,
+           N, K, ldc, tiles_m, tiles, per_xcd, kc_split, sw);
 }
 
 // Tile shapes.  65 rows and more: the one-wave-per-SIMD kernel.  At 33-64 rows 64 x 128 tiles
@@ -638,16 +571,16 @@ TileShape tile_shape(int variant) {
 }
 
 void gemm_bf16_tile(const uint16_t *A, const uint16_t *W, float *C, int M, int N, int K, int ldc, int variant,
-                    int kc_split, RowMaxOut rm, hipStream_t s, SwigluOut sw) {
+                    int kc_split, hipStream_t s, SwigluOut sw) {
   switch (variant) {
-    case 1: launch_wave<2, 2, 3, 2>(A, W, C, M, N, K, ldc, rm, s, kc_split, sw); break;
-    case 4: launch_wave<2, 2, 3, 4>(A, W, C, M, N, K, ldc, rm, s, kc_split, sw); break;
-    case 7: launch_wave<2, 2, 2, 2>(A, W, C, M, N, K, ldc, rm, s, kc_split, sw); break;
-    case 8: launch_wave<2, 2, 2, 4>(A, W, C, M, N, K, ldc, rm, s, kc_split, sw); break;
-    case 13: launch_wave<2, 2, 4, 2>(A, W, C, M, N, K, ldc, rm, s, kc_split, sw); break;
-    case 17: launch_wave<2, 2, 4, 4>(A, W, C, M, N, K, ldc, rm, s, kc_split, sw); break;
-    case 5: launch_tile<1, 4, 1, 2, 4, 4>(A, W, C, M, N, K, ldc, rm, s, kc_split, sw); break;   // 4 waves
-    case 6: launch_tile<2, 4, 1, 1, 4, 4>(A, W, C, M, N, K, ldc, rm, s, kc_split, sw); break;
+    case 1: launch_wave<2, 2, 3, 2>(A, W, C, M, N, K, ldc, s, kc_split, sw); break;
+    case 4: launch_wave<2, 2, 3, 4>(A, W, C, M, N, K, ldc, s, kc_split, sw); break;
+    case 7: launch_wave<2, 2, 2, 2>(A, W, C, M, N, K, ldc, s, kc_split, sw); break;
+    case 8: launch_wave<2, 2, 2, 4>(A, W, C, M, N, K, ldc, s, kc_split, sw); break;
+    case 13: launch_wave<2, 2, 4, 2>(A, W, C, M, N, K, ldc, s, kc_split, sw); break;
+    case 17: launch_wave<2, 2, 4, 4>(A, W, C, M, N, K, ldc, s, kc_split, sw); break;
+    case 5: launch_tile<1, 4, 1, 2, 4, 4>(A, W, C, M, N, K, ldc, s, kc_split, sw); break;   // 4 waves
+    case 6: launch_tile<2, 4, 1, 1, 4, 4>(A, W, C, M, N, K, ldc, s, kc_split, sw); break;
   }
 }
 

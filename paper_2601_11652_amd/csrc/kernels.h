@@ -37,8 +37,7 @@ struct GemmCfg {
 };
 GemmCfg gemm_bf16_plan(int M, int N, int K);
 void gemm_bf16(const uint16_t *A_packed, const uint16_t *W_packed, float *C, int M, int N, int K,
-               int ldc, const GemmCfg &cfg, hipStream_t s, RowMaxOut rm = RowMaxOut{nullptr, nullptr, 0},
-               SwigluOut sw = SwigluOut{nullptr, 0});
+               int ldc, const GemmCfg &cfg, hipStream_t s, SwigluOut sw = SwigluOut{nullptr, 0});
 void gemm_f32(const float *A, const float *W, float *C, int M, int N, int K, int ldc, hipStream_t s);
 // LDS-staged output tiles (both operands staged through LDS): variant 1 is 192 x 128, 4 is
 // 192 x 256, 7 is 128 x 128, 8 is 128 x 256, 13 is 256 x 128 and 17 is 256 x 256 (rows x
@@ -49,7 +48,7 @@ void gemm_f32(const float *A, const float *W, float *C, int M, int N, int K, int
 struct TileShape { int bm, bn, ks, min_k; };
 TileShape tile_shape(int variant);
 void gemm_bf16_tile(const uint16_t *A_packed, const uint16_t *W_packed, float *C, int M, int N, int K, int ldc,
-                    int variant, int kc_split, RowMaxOut rm, hipStream_t s, SwigluOut sw = SwigluOut{nullptr, 0});
+                    int variant, int kc_split, hipStream_t s, SwigluOut sw = SwigluOut{nullptr, 0});
 void pack_linear_bf16(uint16_t *dst, const uint16_t *src, int rows, int cols, hipStream_t s);
 // gate/up weights ([F][d] each) packed with their 32-row blocks interleaved: packed row
 // block 2b = gate rows 32b .. 32b + 31, 2b + 1 = the up rows of the same b
@@ -117,19 +116,19 @@ void attention_f32(const StepDesc &d, int B, const float *q, const float *k_pool
                    hipStream_t s);
 
 // ----- acceptance ----------------------------------------------------------------------------
-struct SamplerScratch {   // carved from the workspace; sizes from sampler_chunks(V)
+struct SamplerScratch {   // carved from the workspace; CH = sampler_chunks(V), RC = sampler_race_chunks(V)
   float *part_m;          // [M][CH] chunk maxima
   int32_t *part_i;        // [M][CH] chunk argmax (greedy)
-  double *part_s;         // [M][CH] chunk sums of exponentials
-  float *race_k;          // [B][CH][2] chunk race winners (p race, residual race)
-  int32_t *race_i;        // [B][CH][2]
+  double *part_s;         // [M][CH] chunk sums of exp(z - the chunk's maximum)
+  float *race_k;          // [B][RC][2] chunk race winners (p race, residual race)
+  int32_t *race_i;        // [B][RC][2]
   int32_t *req_R;         // [B] first rejection
 };
 int sampler_chunks(int V);
-// lm: the LM head's per-tile row maxima of these logits (RowMaxOut), or m == NULL
+int sampler_race_chunks(int V);
 void sampler(const StepDesc &d, int B, int M, int V, const float *logits, const int32_t *tokens,
              const float *q, float T, uint64_t seed, SamplerScratch sc, int32_t *accept_len,
-             int32_t *out_tokens, hipStream_t s, RowMaxOut lm = RowMaxOut{nullptr, nullptr, 0});
+             int32_t *out_tokens, hipStream_t s);
 void uniform_draws(uint64_t seed, uint32_t req, uint32_t tag, uint32_t row, uint32_t n, float *out,
                    hipStream_t s);
 void clear_ints(int *p, int n, hipStream_t s);
