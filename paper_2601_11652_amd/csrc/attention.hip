@@ -379,8 +379,14 @@ void attention_bf16_combine(const StepDesc &d, const AttnGroup *groups, int n_gr
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 path (small models): one workgroup per (request, q head), plain VALU
+// fp32 path (small models): one workgroup per (row, q head), plain VALU
 // ---------------------------------------------------------------------------------------
+// Bound by latency at the sizes it serves (a few rows of contexts of a hundred tokens): every
+// row has its own workgroup, a thread scores one token with 16-byte loads (8 consecutive
+// dims of a K page element are contiguous), and the weighted sum takes 8 consecutive tokens
+// per 32 bytes of a V page, the octets spread over the threads.  (One workgroup per request and
+// head, its rows in turn and one thread per output dim: 144 us per layer at 4 requests of up
+// to 128 tokens.)
 __device__ __forceinline__ float block_reduce_256(float v, float *sh, bool is_max) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -393,62 +399,90 @@ __device__ __forceinline__ float block_reduce_256(float v, float *sh, bool is_ma
   return is_max ? fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3])) : sh[0] + sh[1] + sh[2] + sh[3];
 }
 
+// 8 consecutive floats; V16: 16-byte aligned
+template <bool V16>
+__device__ __forceinline__ void load8(const float *p, float (&v)[8]) {
+  if constexpr (V16) {
+    const float4 a = *reinterpret_cast<const float4 *>(p), b = *reinterpret_cast<const float4 *>(p + 4);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = p[e];
+  }
+}
+
+template <bool V16>
 __global__ __launch_bounds__(256) void attn_f32_kernel(StepDesc d, const float *__restrict__ q,
                                                        const float *__restrict__ kp,
                                                        const float *__restrict__ vp,
                                                        float *__restrict__ out, int nq, int nkv, int hd,
                                                        float scale) {
-  extern __shared__ float sc[];
+  extern __shared__ __attribute__((aligned(16))) float sc[];   // scores, then probabilities, of the row's tokens
   __shared__ float sh[4];
-  const int i = blockIdx.x / nq, hq = blockIdx.x % nq;
-  const int kvh = hq / (nq / nkv);
-  const int nrw = d.nrow[i], ctx = d.ctx[i], off = d.off[i];
+  __shared__ __attribute__((aligned(16))) float qs[256];       // the row's q, later the partial sums
+  const int r = blockIdx.x, hq = blockIdx.y, tid = threadIdx.x;
+  const int i = d.row_req[r], kvh = hq / (nq / nkv);
+  const int T = d.row_pos[r] + 1;                              // causal: keys 0 .. position
   const int32_t *pt = d.page_table + (int64_t)i * d.pt_stride;
   const int page_elems = kPage * hd;
-  for (int j = 0; j < nrw; ++j) {
-    const int64_t r = off + j;
-    const float *qr = q + (r * nq + hq) * hd;
-    const int T = ctx + j + 1;
-    float mx = -INFINITY;
-    for (int t = threadIdx.x; t < T; t += 256) {
-      const int blk = pt[t / kPage];
-      float dot = 0.f;
-      if (blk >= 0 && blk < d.n_blocks) {
-        const float *pg = kp + ((int64_t)blk * nkv + kvh) * page_elems;
-        for (int e = 0; e < hd; ++e) dot += qr[e] * pg[k_page_off(t % kPage, e)];
-      } else {
-        flag_error(d.err, kErrBlock);
+  if (tid < hd) qs[tid] = q[((int64_t)r * nq + hq) * hd + tid];
+  __syncthreads();
+  float mx = -INFINITY;
+  for (int t = tid; t < T; t += 256) {
+    const int blk = pt[t / kPage];
+    float dot = 0.f;
+    if (blk >= 0 && blk < d.n_blocks) {
+      const float *pg = kp + ((int64_t)blk * nkv + kvh) * page_elems;
+      for (int e = 0; e < hd; e += 8) {
+        float k[8];
+        load8<V16>(pg + k_page_off(t % kPage, e), k);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) dot += qs[e + x] * k[x];
       }
-      sc[t] = dot * scale;
-      mx = fmaxf(mx, sc[t]);
+    } else {
+      flag_error(d.err, kErrBlock);
     }
-    mx = block_reduce_256(mx, sh, true);
-    float sum = 0.f;
-    for (int t = threadIdx.x; t < T; t += 256) {
-      const float p = expf(sc[t] - mx);
-      sc[t] = p;
-      sum += p;
+    sc[t] = dot * scale;
+    mx = fmaxf(mx, sc[t]);
+  }
+  mx = block_reduce_256(mx, sh, true);
+  float sum = 0.f;
+  for (int t = tid; t < T; t += 256) {
+    const float p = expf(sc[t] - mx);
+    sc[t] = p;
+    sum += p;
+  }
+  sum = block_reduce_256(sum, sh, false);   // its barriers also publish the probabilities
+  const int groups = max(1, 256 / hd), g = tid / hd, e = tid % hd;   // hd <= 256
+  float acc = 0.f;
+  if (g < groups) {
+    for (int t0 = 8 * g; t0 < T; t0 += 8 * groups) {
+      const int blk = pt[t0 / kPage];
+      if (blk < 0 || blk >= d.n_blocks) continue;
+      float v[8];
+      load8<V16>(vp + ((int64_t)blk * nkv + kvh) * page_elems + v_page_off(t0 % kPage, e), v);
+#pragma unroll
+      for (int x = 0; x < 8; ++x)
+        if (t0 + x < T) acc += sc[t0 + x] * v[x];   // slots past the row's position may hold anything
     }
-    sum = block_reduce_256(sum, sh, false);
-    __syncthreads();
-    for (int e = threadIdx.x; e < hd; e += 256) {
-      float acc = 0.f;
-      for (int t = 0; t < T; ++t) {
-        const int blk = pt[t / kPage];
-        if (blk < 0 || blk >= d.n_blocks) continue;
-        acc += sc[t] * vp[((int64_t)blk * nkv + kvh) * page_elems + v_page_off(t % kPage, e)];
-      }
-      out[(r * nq + hq) * hd + e] = acc / sum;
-    }
-    __syncthreads();
+  }
+  __syncthreads();
+  qs[tid] = acc;
+  __syncthreads();
+  if (tid < hd) {
+    for (int x = 1; x < groups; ++x) acc += qs[x * hd + tid];
+    out[((int64_t)r * nq + hq) * hd + tid] = acc / sum;
   }
 }
 
-void attention_f32(const StepDesc &d, int B, const float *q, const float *k_pool,
+void attention_f32(const StepDesc &d, int M, const float *q, const float *k_pool,
                    const float *v_pool, float *out, int nq, int nkv, int hd, int max_tokens,
                    hipStream_t s) {
   const float scale = 1.0f / sqrtf((float)hd);
-  launch(attn_f32_kernel, B * nq, 256, max_tokens * sizeof(float), s, d, q, k_pool, v_pool, out, nq, nkv, hd, scale);
+  const bool v16 = (((uintptr_t)k_pool | (uintptr_t)v_pool) & 15) == 0;
+  launch(v16 ? attn_f32_kernel<true> : attn_f32_kernel<false>, dim3(M, nq), 256, max_tokens * sizeof(float), s, d, q,
+         k_pool, v_pool, out, nq, nkv, hd, scale);
 }
 
 }  // namespace wisp

@@ -348,48 +348,85 @@ void gemm_bf16(const uint16_t *A, const uint16_t *W, float *C, int M, int N, int
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 path (small models): plain LDS-tiled VALU GEMM, natural row-major operands
+// fp32 path (small models), natural row-major operands: v_mfma_f32_16x16x4_f32
 // ---------------------------------------------------------------------------------------
+// A workgroup owns 16 columns of 16 MT rows and all of K; its 4 waves take every fourth block
+// of 16 K columns and add their sums through LDS in wave order.  Lane l holds columns 4 (l /
+// 16) .. + 3 of a block for row l % 16 (one 16-byte load), and product s of the block takes
+// element s of both operands.  Bound by latency at the few rows this path serves: small column
+// tiles put work on many CUs and PF blocks of loads are in flight per wave.  (32 x 64 tiles with
+// all of K in one workgroup took 92 us at K 1024 and 24 us at K 256, 12 rows.)
+template <int MT, bool V16>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A,
                                                        const float *__restrict__ W,
                                                        float *__restrict__ C, int M, int N, int K,
                                                        int ldc) {
-  constexpr int BM = 32, BN = 64, BK = 16;
-  __shared__ float As[BK][BM + 1];
-  __shared__ float Ws[BK][BN + 1];
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  float acc[2][4] = {};
-  for (int k0 = 0; k0 < K; k0 += BK) {
-    for (int i = tid; i < BM * BK; i += 256) {
-      const int r = i / BK, k = i % BK;
-      As[k][r] = (m0 + r < M && k0 + k < K) ? A[(int64_t)(m0 + r) * K + k0 + k] : 0.f;
+  constexpr int PF = 4;   // K blocks loaded at once
+  __shared__ float part[3][MT][4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16 * MT;
+  const int kl = 4 * (lane >> 4);
+  // rows past the matrix edge re-read the last one (never stored)
+  const float *w = W + (int64_t)min(n0 + (lane & 15), N - 1) * K + kl;
+  const float *a[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) a[i] = A + (int64_t)min(m0 + 16 * i + (lane & 15), M - 1) * K + kl;
+  auto load4 = [](const float *p) {
+    if constexpr (V16) return *reinterpret_cast<const floatx4 *>(p);
+    else return floatx4{p[0], p[1], p[2], p[3]};
+  };
+  floatx4 acc[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int KB = K >> 4;   // K is a multiple of 16
+  for (int b0 = wave; b0 < KB; b0 += 4 * PF) {
+    floatx4 wv[PF], av[PF][MT];
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      const int b = min(b0 + 4 * p, KB - 1);   // blocks past the end are loaded but not used
+      wv[p] = load4(w + 16 * b);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) av[p][i] = load4(a[i] + 16 * b);
     }
-    for (int i = tid; i < BN * BK; i += 256) {
-      const int n = i / BK, k = i % BK;
-      Ws[k][n] = (n0 + n < N && k0 + k < K) ? W[(int64_t)(n0 + n) * K + k0 + k] : 0.f;
+#pragma unroll
+    for (int p = 0; p < PF; ++p) {
+      if (b0 + 4 * p >= KB) break;
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[p][s], av[p][i][s], acc[i], 0, 0, 0);
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < BK; ++k)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += As[k][ty * 2 + i] * Ws[k][tx * 4 + j];
-    __syncthreads();
   }
+  if (wave > 0) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int r = m0 + ty * 2 + i, c = n0 + tx * 4 + j;
-      if (r < M && c < N) C[(int64_t)r * ldc + c] = acc[i][j];
+      for (int e = 0; e < 4; ++e) part[wave - 1][i][e][lane] = acc[i][e];
+  }
+  __syncthreads();
+  if (wave > 0) return;
+  // lane l: row l % 16, columns 4 (l / 16) + e of each 16 x 16 block
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const int r = m0 + 16 * i + (lane & 15);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int c = n0 + 4 * (lane >> 4) + e;
+      const float v = ((acc[i][e] + part[0][i][e][lane]) + part[1][i][e][lane]) + part[2][i][e][lane];
+      if (r < M && c < N) C[(int64_t)r * ldc + c] = v;
     }
+  }
 }
 
 void gemm_f32(const float *A, const float *W, float *C, int M, int N, int K, int ldc, hipStream_t s) {
-  dim3 grid((N + 63) / 64, (M + 31) / 32, 1);
-  launch(gemm_f32_kernel, grid, 256, 0, s, A, W, C, M, N, K, ldc);
+  const bool v16 = (((uintptr_t)A | (uintptr_t)W) & 15) == 0;   // rows are multiples of 16 floats
+  const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4;
+  const dim3 grid((N + 15) / 16, (M + 16 * mt - 1) / (16 * mt), 1);
+  auto go = [&](auto kernel) { launch(kernel, grid, 256, 0, s, A, W, C, M, N, K, ldc); };
+  if (mt == 1) go(v16 ? gemm_f32_kernel<1, true> : gemm_f32_kernel<1, false>);
+  else if (mt == 2) go(v16 ? gemm_f32_kernel<2, true> : gemm_f32_kernel<2, false>);
+  else go(v16 ? gemm_f32_kernel<4, true> : gemm_f32_kernel<4, false>);
 }
 
 // ---------------------------------------------------------------------------------------

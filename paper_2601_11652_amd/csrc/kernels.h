@@ -111,7 +111,7 @@ void attention_bf16_main(const StepDesc &d, const AttnItem *items, int n_items, 
 void attention_bf16_combine(const StepDesc &d, const AttnGroup *groups, int n_groups, int max_group_chunks,
                             const float *part_o, const float *part_ml, uint16_t *out, bool out_packed,
                             int out_K, int nq, int nkv, int hd, hipStream_t s);
-void attention_f32(const StepDesc &d, int B, const float *q, const float *k_pool,
+void attention_f32(const StepDesc &d, int M, const float *q, const float *k_pool,
                    const float *v_pool, float *out, int nq, int nkv, int hd, int max_tokens,
                    hipStream_t s);
 

@@ -552,7 +552,7 @@ wisp_status run_forward(const Plan &p, const wisp_model *m, const wisp_kv *kv, c
                              p.nkv, p.hd, s);
     } else {
       ProfScope ps(WISP_PROF_ATTN, attn_bytes, attn_flops, s);
-      attention_f32(sd, p.B, (const float *)qb, (const float *)kl, (const float *)vl, (float *)ao, p.nq,
+      attention_f32(sd, p.M, (const float *)qb, (const float *)kl, (const float *)vl, (float *)ao, p.nq,
                     p.nkv, p.hd, p.max_tokens, s);
     }
     const int so = gemm(ao, m->w_o[l], part, p.d, p.qdim, p.g_o);
@@ -893,7 +893,7 @@ wisp_status wisp_attention(const wisp_model *model, const wisp_kv *kv, const wis
       attention_bf16_combine(sd, groups, (int)p.groups.size(), p.max_group_chunks, po, pml, (uint16_t *)out, false, p.qdim, p.nq,
                              p.nkv, p.hd, s);
     } else {
-      attention_f32(sd, p.B, (const float *)q, (const float *)kv->k_pool, (const float *)kv->v_pool,
+      attention_f32(sd, p.M, (const float *)q, (const float *)kv->k_pool, (const float *)kv->v_pool,
                     (float *)out, p.nq, p.nkv, p.hd, p.max_tokens, s);
     }
     return hip_check("attention launch");
