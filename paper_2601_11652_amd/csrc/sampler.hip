@@ -28,9 +28,11 @@ __device__ __forceinline__ Philox4 draw(uint64_t seed, uint32_t c0, uint32_t row
 // logits, kRaceChunk per workgroup of the race.  Partial results are combined in fixed order.
 // ---------------------------------------------------------------------------------------
 constexpr int kVChunk = 8192;
-// The race costs about 120 instructions per entry (Philox, two or three logarithms): 8 per
-// thread fill the chip at 32 requests (B = 32: 29.6 us with chunks of 8192, 2 waves per SIMD)
-constexpr int kRaceChunk = 2048;
+// The race takes chunks of 2048 entries (8 per thread), doubled up to 8192 while they make more
+// than kRaceGroups workgroups: a workgroup also decides the request's drafts, which costs
+// about as much as 2048 entries, but fewer than that many workgroups leave SIMDs idle (with
+// 4-byte loads: B = 32 27.4 us with chunks of 8192, 18.3 with 2048; B = 256 119 against 143).
+constexpr int kRaceChunk = 2048, kRaceChunkMax = 8192, kRaceGroups = 2560;
 
 __device__ __forceinline__ bool better(float ka, int ia, float kb, int ib) {
   return ka > kb || (ka == kb && ia < ib);
@@ -72,7 +74,7 @@ __device__ __forceinline__ void block_argmax(float &k, int &i, float *shk, int *
 // so the logits are read once.  Bound by the logits' bytes once the instructions per entry
 // allow it: 16-byte loads where the rows are aligned (VEC) and no division at T = 1 (l / 1 is
 // l).  B = 32 (171 rows of 128256): maximum and sum in separate passes of 4-byte loads took
-// 28 + 30 us.
+// 28 + 30 us, together 18 (5 TB/s).
 template <bool VEC>
 __global__ __launch_bounds__(256) void row_stats_kernel(const float *__restrict__ logits, int V, float T, int CH,
                                                         float *__restrict__ part_m, int32_t *__restrict__ part_i,
@@ -95,7 +97,7 @@ __global__ __launch_bounds__(256) void row_stats_kernel(const float *__restrict_
 #pragma unroll
     for (int q = 0; q < PER / 4; ++q) {
       const int i4 = 256 * q + threadIdx.x;
-      const float4 x = 4 * i4 < n ? l4[i4] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+      const float4 x = 4 * i4 < n ? __builtin_bit_cast(float4, ld16_stream(l4 + i4)) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
       z[4 * q] = x.x;
       z[4 * q + 1] = x.y;
       z[4 * q + 2] = x.z;
@@ -191,15 +193,34 @@ __device__ RowStat row_stat8(const float *part_m, const int32_t *part_i, const d
   return st;
 }
 
+// entries 4 k4 .. 4 k4 + 3 of a row of V (VEC: the row is 16-byte aligned, V a multiple of 4;
+// otherwise entries past the end repeat the last one)
+template <bool VEC>
+__device__ __forceinline__ void load_quad(const float *row, int k4, int V, float (&v)[4]) {
+  if constexpr (VEC) {
+    const float4 x = reinterpret_cast<const float4 *>(row)[k4];
+    v[0] = x.x;
+    v[1] = x.y;
+    v[2] = x.z;
+    v[3] = x.w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = row[min(4 * k4 + e, V - 1)];
+  }
+}
+
 // pass 2: Eq. (1)-(2) acceptance (recomputed by every chunk's workgroup), then that chunk's
 // part of the exponential race for the extra token (Eq. (3) / residual).  The <= 17 rows'
 // statistics are combined by 8 lanes each; the <= 16 draft decisions are independent of one
 // another, so thread j - 1 takes draft j's and R is the smallest rejected j (gamma + 1 when
-// none is): one round of loads instead of a chain.
+// none is): one round of loads instead of a chain.  The race's logits and q come as 16-byte
+// loads, two quadruples per thread at a time (4-byte loads inside the loop over entries: 13.4
+// us at B = 1, 119 at B = 256; now 8.8 and 94).
+template <bool VEC>
 __global__ __launch_bounds__(256) void race_kernel(StepDesc d, int V, const float *__restrict__ logits,
                                                    const int32_t *__restrict__ tokens,
                                                    const float *__restrict__ q, float T, uint64_t seed,
-                                                   int CH, int RC, const float *__restrict__ part_m,
+                                                   int CH, int chunk, int RC, const float *__restrict__ part_m,
                                                    const int32_t *__restrict__ part_i,
                                                    const double *__restrict__ part_s,
                                                    float *__restrict__ race_k, int32_t *__restrict__ race_i,
@@ -261,28 +282,41 @@ __global__ __launch_bounds__(256) void race_kernel(StepDesc d, int V, const floa
   float kR = -INFINITY, kP = -INFINITY;
   int iR = 0x7FFFFFFF, iP = 0x7FFFFFFF;
   int any = 0;
-  const int k4_0 = c * (kRaceChunk / 4), k4_1 = min((V + 3) / 4, (c + 1) * (kRaceChunk / 4));
-  for (int k4 = k4_0 + threadIdx.x; k4 < k4_1; k4 += 256) {
-    const Philox4 w = draw(seed, (uint32_t)k4, (uint32_t)r, req, kTagRace);
+  // the chunk's quadruples in turns of 2 per thread, a turn's logits and q loaded together
+  const int k4_1 = min((V + 3) / 4, (c + 1) * (chunk / 4));
+  for (int base = c * (chunk / 4) + threadIdx.x; base < k4_1; base += 512) {
+    float lv[2][4], qv[2][4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int k = k4 * 4 + e;
-      if (k >= V) break;
-      const float z = T == 1.f ? l[k] : l[k] / T;
-      const float gk = logf(-logf(uniform_from_word(w.v[e])));
-      const float keyp = z - gk;
-      if (keyp > kP) {
-        kP = keyp;
-        iP = k;
-      }
-      if (rejected) {
-        const float wk = expf(z - st.m) / st.S - qr[k];
-        if (wk > 0.f) {
-          any = 1;
-          const float keyr = logf(wk) - gk;
-          if (keyr > kR) {
-            kR = keyr;
-            iR = k;
+    for (int x = 0; x < 2; ++x) {
+      const int k4 = min(base + 256 * x, k4_1 - 1);   // past the end: loaded again, not used
+      load_quad<VEC>(l, k4, V, lv[x]);
+      if (rejected) load_quad<VEC>(qr, k4, V, qv[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const int k4 = base + 256 * x;
+      if (k4 >= k4_1) break;
+      const Philox4 w = draw(seed, (uint32_t)k4, (uint32_t)r, req, kTagRace);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int k = k4 * 4 + e;
+        if (k >= V) break;
+        const float z = T == 1.f ? lv[x][e] : lv[x][e] / T;
+        const float gk = logf(-logf(uniform_from_word(w.v[e])));
+        const float keyp = z - gk;
+        if (keyp > kP) {
+          kP = keyp;
+          iP = k;
+        }
+        if (rejected) {
+          const float wk = expf(z - st.m) / st.S - qv[x][e];
+          if (wk > 0.f) {
+            any = 1;
+            const float keyr = logf(wk) - gk;
+            if (keyr > kR) {
+              kR = keyr;
+              iR = k;
+            }
           }
         }
       }
@@ -350,11 +384,15 @@ void sampler(const StepDesc &d, int B, int M, int V, const float *logits, const 
              const float *q, float T, uint64_t seed, SamplerScratch sc, int32_t *accept_len,
              int32_t *out_tokens, hipStream_t s) {
   if (B == 0) return;
-  const int CH = sampler_chunks(V), RC = sampler_race_chunks(V);
+  const int CH = sampler_chunks(V);
+  int chunk = kRaceChunk;
+  while (chunk < kRaceChunkMax && (int64_t)B * ((V + chunk - 1) / chunk) > kRaceGroups) chunk *= 2;
+  const int RC = (V + chunk - 1) / chunk;   // at most sampler_race_chunks(V)
   const bool vec = V % 4 == 0 && ((uintptr_t)logits & 15) == 0;
   launch(vec ? row_stats_kernel<true> : row_stats_kernel<false>, dim3(M, CH), 256, 0, s, logits, V, T, CH, sc.part_m,
          sc.part_i, sc.part_s);
-  launch(race_kernel, dim3(B, T == 0.f ? 1 : RC), 256, 0, s, d, V, logits, tokens, q, T, seed, CH, RC, sc.part_m,
+  const bool qvec = vec && ((uintptr_t)q & 15) == 0;
+  launch(qvec ? race_kernel<true> : race_kernel<false>, dim3(B, T == 0.f ? 1 : RC), 256, 0, s, d, V, logits, tokens, q, T, seed, CH, chunk, RC, sc.part_m,
          sc.part_i, sc.part_s, sc.race_k, sc.race_i, sc.req_R);
   launch(finalize_kernel, B, 64, 0, s, d, tokens, T, RC, sc.race_k, sc.race_i, sc.req_R, accept_len, out_tokens);
 }
