@@ -58,6 +58,16 @@ __device__ __forceinline__ uint4 ld16_stream(const void *p) {
   const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+// One 16-byte-per-lane load from global memory straight into LDS: lane l's 16 bytes land at
+// dst + 16 l (dst wave-uniform, passed in M0).  Issued as inline assembly: the compiler then
+// inserts no wait of its own before later LDS reads (it would otherwise assume any such
+// load in flight may alias them and wait for all of them), and the kernel waits on the
+// vector-memory counter itself, which runs in issue order.
+__device__ __forceinline__ void lds_dma16(const void *src, const void *dst) {
+  // dst is wave-uniform by construction; readfirstlane makes that visible to the compiler
+  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)dst);
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(m0) : "memory", "m0");
+}
 // zero unless `ok` (the load itself is issued unconditionally from a valid address)
 __device__ __forceinline__ uint4 keep_if(bool ok, uint4 v) {
   return ok ? v : make_uint4(0, 0, 0, 0);

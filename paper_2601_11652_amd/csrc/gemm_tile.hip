@@ -26,17 +26,6 @@ __device__ __forceinline__ void static_for(F &&f) {
   }
 }
 
-// One 16-byte-per-lane load from global memory straight into LDS: lane l's 16 bytes land at
-// dst + 16 l (dst wave-uniform, passed in M0).  Issued as inline assembly: the compiler then
-// inserts no wait of its own before later LDS reads (it would otherwise assume any such
-// load in flight may alias them and wait for all of them), and the kernel waits on the
-// vector-memory counter itself, counting exactly the loads it issued.  The kernel issues
-// no other vector-memory operation while such loads are in flight.
-__device__ __forceinline__ void lds_dma16(const void *src, const void *dst) {
-  // dst is wave-uniform by construction; readfirstlane makes that visible to the compiler
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)dst);
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(m0) : "memory", "m0");
-}
 // the same for data read once (the weight stream): marked non-temporal, so the caches do
 // not keep it at the expense of the activation slices that the other tiles re-read (measured
 // on weight-heavy tiles: the weight stream runs about a third faster)

@@ -92,24 +92,27 @@ template <typename T>
 void swiglu(const float *part, int splits, T *out, bool packed, int M, int F, bool interleaved, hipStream_t s);
 
 // ----- attention ---------------------------------------------------------------------------
-struct AttnItem {   // one wave's work: request, kv head, row group, token range
-  int32_t req, kvh_rbg, t0, t1;
+struct AttnItem {   // a run of one wave's work: request, kv head, row group, token range
+  int32_t req, kvh_rbg, t0, t1;   // t0 a multiple of 32, plus kAttnWhole
 };
-struct AttnGroup {  // the chunks of one (request, kv head, row group), combined in order
-  int32_t req, kvh, rbg, first_item, n_items, pad0, pad1, pad2;
+struct AttnGroup {  // the items (at least two) of one (request, kv head, row group), combined in order
+  int32_t req, kvh_rbg, first_item, n_items;
 };
-constexpr int kAttnRowsPerItem = 48;   // query rows one wave carries (3 blocks of 16)
 constexpr int kAttnMaxItems = 1 << 22;  // split-KV work items of one call (int indices, workspace)
 constexpr int kAcceptRowsMax = 1 << 29; // rows of one acceptance-only call (int offsets)
-constexpr int kAttnMaxChunkPages = 64; // pages of one item (one block id per lane)
-constexpr int kAttnCombineChunks = 8;  // chunks the combine loads per round of dependent loads
+constexpr int kAttnWhole = 1;          // flag in AttnItem::t0: the item is its group's only one
+constexpr int kAttnWindowPages = 64;   // pages whose block ids a wave holds (one per lane)
+constexpr int kAttnCombineChunks = 8;  // partials the combine loads per round of dependent loads
 
-// split-KV partials of every item, then their fixed-order combine into `out`
-void attention_bf16_main(const StepDesc &d, const AttnItem *items, int n_items, const uint16_t *q,
-                         const uint16_t *k_pool, const uint16_t *v_pool, float *part_o, float *part_ml,
-                         int nq, int nkv, int hd, hipStream_t s);
-void attention_bf16_combine(const StepDesc &d, const AttnGroup *groups, int n_groups, int max_group_chunks,
-                            const float *part_o, const float *part_ml, uint16_t *out, bool out_packed,
+// split-KV partials of every item (wave w runs items first[w] .. first[w + 1] - 1, or item w if
+// first is null), then their
+// fixed-order combine into `out`
+void attention_bf16_main(const StepDesc &d, const AttnItem *items, const int32_t *first, int n_waves, int item_rows,
+                         const uint16_t *q, const uint16_t *k_pool, const uint16_t *v_pool, float *part_o,
+                         float *part_ml, uint16_t *out, bool out_packed, int out_K, int nq, int nkv, int hd,
+                         hipStream_t s);
+void attention_bf16_combine(const StepDesc &d, const AttnGroup *groups, int n_groups, int item_rows,
+                            int max_group_chunks, const float *part_o, const float *part_ml, uint16_t *out, bool out_packed,
                             int out_K, int nq, int nkv, int hd, hipStream_t s);
 void attention_f32(const StepDesc &d, int M, const float *q, const float *k_pool,
                    const float *v_pool, float *out, int nq, int nkv, int hd, int max_tokens,

@@ -48,10 +48,13 @@ struct Plan {
   GemmCfg g_qkv{}, g_o{}, g_gu{}, g_down{}, g_lm{};
   std::vector<AttnItem> items;
   std::vector<AttnGroup> groups;
+  std::vector<int32_t> first;        // wave w runs items first[w] .. first[w + 1] - 1 (empty: item w)
+  int attn_waves() const { return (int)(first.empty() ? items.size() : first.size() - 1); }
+  int item_rows = 0;                 // query rows of an item: 32, 48 or 64
   std::vector<int32_t> host;         // descriptor block uploaded to the device
   // int32 offsets inside the descriptor block
   size_t i_off = 0, i_doff = 0, i_gamma = 0, i_ctx = 0, i_req = 0, i_row_req = 0, i_row_pos = 0,
-         i_items = 0, i_groups = 0, i_voff = 0, i_nrow = 0, i_vrow = 0;
+         i_items = 0, i_groups = 0, i_first = 0, i_voff = 0, i_nrow = 0, i_vrow = 0;
   // byte offsets inside the workspace
   size_t w_err = 0, w_desc = 0, w_rope = 0, w_h = 0, w_xn = 0, w_ao = 0, w_af = 0, w_q = 0,
          w_part = 0, w_attn_o = 0, w_attn_ml = 0, w_sm = 0, w_si = 0, w_ss = 0, w_rk = 0, w_ri = 0,
@@ -126,7 +129,6 @@ void carve(size_t &w, size_t &field, size_t bytes) {
   w = align256(w + bytes);
 }
 
-// forward=true: the full step; false: acceptance only (rows/drafts of the batch, vocab V)
 // compute units of the current device (the attention work list is sized to them)
 int device_cus() {
   int dev = 0, n = 0;
@@ -136,6 +138,142 @@ int device_cus() {
   return n;
 }
 
+// Attention work list.  A row group (item_rows of a request's rows x G query rows of one kv
+// head) attends to a run of page pairs; the waves share all groups' pairs in order (request,
+// kv head, row group), and a group that one wave covers alone needs no combine.
+wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<int> &nrow) {
+  const int64_t slots = 4 * (int64_t)device_cus();   // one wave per SIMD
+  // a row group's keys end at its last row's causal limit (prompt rows see fewer)
+  auto group_tokens = [&](int i, int g, int R) {
+    const int last = std::min(nrow[i] * p.G, (g + 1) * R) - 1;
+    return d->ctx_len[i] + last / p.G + 1;
+  };
+  auto group_pairs = [&](int i, int g, int R) { return (group_tokens(i, g, R) + 31) / 32; };
+  auto row_groups = [&](int i, int R) { return (nrow[i] * p.G + R - 1) / R; };
+
+  // the largest batch accepted: 2^22 items of at most 48 query rows and 32 page pairs, a round
+  // of wave slots kept back (indices are int: what is built below is at most twice as long)
+  int64_t fewest = 0;
+  // Query rows per item, by the time of all pairs at the rates measured per pair and launch
+  // (ns).  A pair that comes from memory: 2.7 with 32 rows (two waves per SIMD), 2.95 and 3.0
+  // with 48 and 64, so as few groups per request as fit; past 256 rows (prompts: neighbouring
+  // groups share the pairs through L2) the products bound it: 1.4, 2.4 and 3.3, so 32 rows.
+  // (4096 prompt rows: 364 us per layer with 32 rows, 436 with 64; 128 requests of up to 68
+  // rows: 623 us with 48, 590 with 64; 32 of up to 36 rows: 38 us with 32, 30 with 48.)
+  constexpr int kRows[3] = {32, 48, 64};
+  constexpr double kStream[3] = {2.7, 2.95, 3.0}, kCompute[3] = {1.4, 2.4, 3.3};
+  double us[3] = {0, 0, 0};
+  for (int i = 0; i < p.B; ++i) {
+    const bool prompt = nrow[i] * p.G > 256;
+    for (int r = 0; r < 3; ++r) {
+      int64_t pairs = 0;
+      for (int g = 0, n = row_groups(i, kRows[r]); g < n; ++g) {
+        const int pr = group_pairs(i, g, kRows[r]);
+        pairs += pr;
+        if (kRows[r] == 48) fewest += (int64_t)p.nkv * ((pr + 31) / 32);
+      }
+      us[r] += pairs * (prompt ? kCompute[r] : kStream[r]);
+    }
+  }
+  if (fewest > kAttnMaxItems - slots)
+    return fail(WISP_E_UNSUPPORTED, "the batch's contexts need %lld attention work items (at most %d)",
+                (long long)fewest, kAttnMaxItems - (int)slots);
+  const int best = us[0] <= us[1] && us[0] <= us[2] ? 0 : us[1] <= us[2] ? 1 : 2;
+  const int R = p.item_rows = kRows[best];
+
+  int64_t total = 0, most = 0, n_groups = 0;   // page pairs of all groups, of the longest; per kv head
+  for (int i = 0; i < p.B; ++i)
+    for (int g = 0, n = row_groups(i, R); g < n; ++g, ++n_groups) {
+      const int64_t pr = group_pairs(i, g, R);
+      total += p.nkv * pr;
+      most = std::max(most, pr);
+    }
+  auto count_items = [&](int64_t L) {
+    int64_t n = 0;
+    for (int i = 0; i < p.B; ++i)
+      for (int g = 0, m = row_groups(i, R); g < m; ++g) n += p.nkv * ((group_pairs(i, g, R) + L - 1) / L);
+    return n;
+  };
+  // One item per wave while that takes items of at most 16 pairs: a group's pairs cut into equal
+  // parts of at most L, L the shortest whose items fit one wave per SIMD or, with 32 rows, two.
+  // (Two on some SIMDs only are slower than one on each: 32 requests of 0.5-2k 30 us per layer
+  // in 1008 items, 38 in 1200; 64 of 0.5-4k 85 us in 2032, 106 in 1032.)  If 16 pairs do not
+  // fit, the groups themselves are many, and the left-over workgroups start as others end.
+  // Beyond that, equal shares of all pairs per wave (64 of 0.5-4k, 14 pairs per wave: 91
+  // instead of 85 us; 4 prompts of 512: 55 instead of 43; 256 of 1-8k, 110 per wave: 610
+  // instead of 692).
+  constexpr int64_t kShort = 16;
+  const bool few = total <= kShort * slots && count_items(kShort) <= slots;
+  const int64_t waves = std::max<int64_t>(1, std::min(R == 32 && !few ? 2 * slots : slots, total));
+  const bool single = total <= kShort * waves;
+  int64_t L = std::max<int64_t>(2, (total + waves - 1) / waves);
+  if (single)
+    while (L < kShort && count_items(L) > waves) ++L;
+  if (few) {
+    // Small batches leave wave slots idle even at the shortest items, and their step is
+    // latency-bound: longer items then cost little, while a group of more than
+    // kAttnCombineChunks chunks costs the combine further dependent loads.  Whenever the
+    // items still fit one round of the wave slots, they grow until no group has more
+    // than kAttnCombineChunks of them (B = 1: attention + combine 10.4 + 13.9 -> 14.3 +
+    // 4.2 us per layer; B = 16: 27.7 -> 25.5 us; B = 4 and 8 within 3 %).
+    const int64_t Lc = std::min<int64_t>(kAttnWindowPages / 2, std::max(L, (most + kAttnCombineChunks - 1) / kAttnCombineChunks));
+    if (count_items(Lc) <= slots) L = Lc;
+  }
+  // shares: wave w starts at pair w * total / waves, moved to a group's edge if one is within
+  // 1/16 of a share (a sliver of a group costs an item and a partial, 1/16 more a little time)
+  const int64_t snap = total / waves / 16;
+  int64_t at = 0, w = 0;       // pairs before this group; wave of the last item
+  auto start = [&](int64_t k) { return k * total / waves; };
+  p.items.reserve(single ? count_items(L) : waves + (int64_t)p.nkv * n_groups);
+  if (!single) {
+    p.first.reserve(waves + 1);
+    p.first.push_back(0);
+  }
+  for (int i = 0; i < p.B; ++i) {
+    const int nrbg = row_groups(i, R);
+    for (int h = 0; h < p.nkv; ++h)
+      for (int g = 0; g < nrbg; ++g) {
+        const int T = group_tokens(i, g, R), pairs = (T + 31) / 32;
+        AttnGroup gr{};
+        gr.req = i;
+        gr.kvh_rbg = (int32_t)((uint32_t)h | (uint32_t)g << 16);
+        gr.first_item = (int32_t)p.items.size();
+        auto item = [&](int64_t a, int64_t b) {
+          AttnItem it{};
+          it.req = i;
+          it.kvh_rbg = gr.kvh_rbg;
+          it.t0 = 32 * (int)a | (a == 0 && b == pairs ? kAttnWhole : 0);
+          it.t1 = std::min(T, 32 * (int)b);
+          p.items.push_back(it);
+        };
+        if (single) {
+          const int64_t n = (pairs + L - 1) / L;
+          for (int64_t k = 0; k < n; ++k) item(k * pairs / n, (k + 1) * pairs / n);
+        } else {
+          int64_t a = 0;
+          while (w + 1 < waves && start(w + 1) < at + pairs + snap) {   // waves that start in this group
+            const int64_t b = start(w + 1) - at;
+            if (b >= pairs - snap) break;              // at its end: the next group's first
+            if (b > a && b > snap) {
+              item(a, b);
+              a = b;
+            }
+            p.first.push_back((int32_t)p.items.size());
+            ++w;
+          }
+          item(a, pairs);
+          at += pairs;
+        }
+        gr.n_items = (int32_t)p.items.size() - gr.first_item;
+        p.max_group_chunks = std::max(p.max_group_chunks, (int)gr.n_items);
+        if (gr.n_items > 1) p.groups.push_back(gr);
+      }
+  }
+  if (!single) p.first.push_back((int32_t)p.items.size());
+  return WISP_OK;
+}
+
+// forward=true: the full step; false: acceptance only (rows/drafts of the batch, vocab V)
 wisp_status make_plan(Plan &p, const wisp_model *m, const wisp_batch_desc *d, bool forward, int vocab = 0) {
   p.B = d->B;
   p.V = forward ? m->vocab : vocab;
@@ -175,83 +313,8 @@ wisp_status make_plan(Plan &p, const wisp_model *m, const wisp_batch_desc *d, bo
       p.g_lm = gemm_bf16_plan(p.Mv, p.V, p.d);
       p.g_lm.splits = 1;
       p.g_lm.kf_per_split = p.d / 16;
-      // split-KV work list: items of <= 48 query rows and a run of page pairs.  One wave per
-      // item and one 4-wave workgroup per CU are resident at a time, so a round started by
-      // a few left-over workgroups would double the kernel's time; an item spans at most
-      // kAttnMaxChunkPages pages, whose block ids one wave keeps in a register.
-      const int64_t slots = 4 * (int64_t)device_cus();
-      // items of a group: its page pairs split into n equal parts (n = ceil(pairs / L)),
-      // L being the shortest item length (in pairs) whose items fill whole rounds of the
-      // device's wave slots; equal parts keep every wave's item close to L pairs, so no
-      // wave waits on a longer one
-      // a row group's keys end at its last row's causal limit (prompt rows see fewer)
-      auto group_tokens = [&](int i, int g) {
-        const int rows = nrow[i] * p.G;
-        const int last = std::min(rows, (g + 1) * kAttnRowsPerItem) - 1;
-        return d->ctx_len[i] + last / p.G + 1;
-      };
-      auto count_items = [&](int L) {
-        int64_t n = 0;
-        for (int i = 0; i < p.B; ++i) {
-          const int nrbg = (nrow[i] * p.G + kAttnRowsPerItem - 1) / kAttnRowsPerItem;
-          for (int g = 0; g < nrbg; ++g) {
-            const int64_t pairs = (group_tokens(i, g) + 31) / 32;
-            n += (int64_t)p.nkv * ((pairs + L - 1) / L);
-          }
-        }
-        return n;
-      };
-      const int L_max = kAttnMaxChunkPages / 2;
-      int64_t rounds = 1;
-      const int64_t fewest = count_items(L_max);
-      // the work list holds at most fewest + slots items (below); its indices are int
-      if (fewest > kAttnMaxItems - slots)
-        return fail(WISP_E_UNSUPPORTED, "the batch's contexts need %lld attention work items (at most %d)",
-                    (long long)fewest, kAttnMaxItems - (int)slots);
-      while (rounds * slots < fewest) ++rounds;
-      int L = 2;
-      while (L < L_max && count_items(L) > rounds * slots) ++L;
-      // Small batches leave wave slots idle even at the shortest items, and their step is
-      // latency-bound: longer items then cost little, while a group of more than
-      // kAttnCombineChunks chunks costs the combine further dependent loads.  Whenever the
-      // items still fit one round of the wave slots, they grow until no group has more
-      // than kAttnCombineChunks of them (B = 1: attention + combine 10.4 + 13.9 -> 14.3 +
-      // 4.2 us per layer; B = 16: 27.7 -> 25.5 us; B = 4 and 8 within 3 %).
-      {
-        int64_t most = 0;
-        for (int i = 0; i < p.B; ++i) {
-          const int nrbg = (nrow[i] * p.G + kAttnRowsPerItem - 1) / kAttnRowsPerItem;
-          for (int g = 0; g < nrbg; ++g) most = std::max<int64_t>(most, (group_tokens(i, g) + 31) / 32);
-        }
-        const int Lc = (int)std::min<int64_t>(L_max, std::max<int64_t>(L, (most + kAttnCombineChunks - 1) / kAttnCombineChunks));
-        if (count_items(Lc) <= slots) L = Lc;
-      }
-      for (int i = 0; i < p.B; ++i) {
-        const int rows = nrow[i] * p.G;
-        const int nrbg = (rows + kAttnRowsPerItem - 1) / kAttnRowsPerItem;
-        for (int h = 0; h < p.nkv; ++h)
-          for (int g = 0; g < nrbg; ++g) {
-            const int T = group_tokens(i, g);
-            const int pairs = (T + 31) / 32;
-            const int n = (pairs + L - 1) / L;
-            AttnGroup gr{};
-            gr.req = i;
-            gr.kvh = h;
-            gr.rbg = g;
-            gr.first_item = (int32_t)p.items.size();
-            for (int k = 0; k < n; ++k) {
-              AttnItem it{};
-              it.req = i;
-              it.kvh_rbg = h | (g << 16);
-              it.t0 = 32 * (int)((int64_t)k * pairs / n);
-              it.t1 = std::min(T, 32 * (int)((int64_t)(k + 1) * pairs / n));
-              p.items.push_back(it);
-            }
-            gr.n_items = (int32_t)p.items.size() - gr.first_item;
-            p.max_group_chunks = std::max(p.max_group_chunks, (int)gr.n_items);
-            p.groups.push_back(gr);
-          }
-      }
+      wisp_status st = plan_attention(p, d, nrow);
+      if (st != WISP_OK) return st;
     }
   }
   // descriptor block
@@ -267,8 +330,9 @@ wisp_status make_plan(Plan &p, const wisp_model *m, const wisp_batch_desc *d, bo
   take(p.i_req, p.B);
   take(p.i_row_req, p.M);
   take(p.i_row_pos, p.M);
-  take(p.i_items, p.items.size() * 4);
-  take(p.i_groups, p.groups.size() * 8);
+  take(p.i_items, p.items.size() * (sizeof(AttnItem) / 4));
+  take(p.i_groups, p.groups.size() * (sizeof(AttnGroup) / 4));
+  take(p.i_first, p.first.size());
   take(p.i_voff, p.B + 1);
   take(p.i_nrow, p.B);
   take(p.i_vrow, p.Mv);
@@ -290,6 +354,7 @@ wisp_status make_plan(Plan &p, const wisp_model *m, const wisp_batch_desc *d, bo
     for (int j = 0; j <= d->gamma[i]; ++j) p.host[p.i_vrow + voff[i] + j] = off[i + 1] - (d->gamma[i] + 1) + j;
   }
   if (!p.items.empty()) std::memcpy(&p.host[p.i_items], p.items.data(), p.items.size() * sizeof(AttnItem));
+  std::copy(p.first.begin(), p.first.end(), p.host.begin() + p.i_first);
   if (!p.groups.empty()) std::memcpy(&p.host[p.i_groups], p.groups.data(), p.groups.size() * sizeof(AttnGroup));
 
   // workspace
@@ -321,8 +386,8 @@ wisp_status make_plan(Plan &p, const wisp_model *m, const wisp_batch_desc *d, bo
       part = std::max({(size_t)p.qkvN, (size_t)p.d, (size_t)2 * p.F});
     }
     carve(w, p.w_part, part * p.M * 4);
-    carve(w, p.w_attn_o, p.items.size() * (size_t)p.hd * 64 * 4);
-    carve(w, p.w_attn_ml, p.items.size() * 64 * 2 * 4);
+    carve(w, p.w_attn_o, p.items.size() * (size_t)p.hd * p.item_rows * 4);
+    carve(w, p.w_attn_ml, p.items.size() * (size_t)p.item_rows * 2 * 4);
   }
   p.total = w;
   return WISP_OK;
@@ -499,6 +564,7 @@ wisp_status run_forward(const Plan &p, const wisp_model *m, const wisp_kv *kv, c
   const int64_t layer_elems = (int64_t)kv->n_blocks * p.nkv * WISP_PAGE * p.hd;
   const AttnItem *items = reinterpret_cast<const AttnItem *>(ws + p.w_desc + p.i_items * 4);
   const AttnGroup *groups = reinterpret_cast<const AttnGroup *>(ws + p.w_desc + p.i_groups * 4);
+  const int32_t *first = p.first.empty() ? nullptr : reinterpret_cast<const int32_t *>(ws + p.w_desc) + p.i_first;
   const int32_t *vrow = reinterpret_cast<const int32_t *>(ws + p.w_desc) + p.i_vrow;
 
   const double es = p.bf16 ? 2.0 : 4.0;
@@ -511,10 +577,10 @@ wisp_status run_forward(const Plan &p, const wisp_model *m, const wisp_kv *kv, c
   for (const AttnItem &it : p.items) {
     const int G = p.G;
     const int rows = (int)p.host[p.i_nrow + it.req];
-    const int rbg = it.kvh_rbg >> 16;
-    const int nr = std::min(kAttnRowsPerItem, rows * G - rbg * kAttnRowsPerItem);
-    if (rbg == 0) attn_bytes += (double)(it.t1 - it.t0) * kv_tok / p.nkv;
-    attn_flops += 4.0 * p.hd * nr * (it.t1 - it.t0);
+    const int rbg = (int)((uint32_t)it.kvh_rbg >> 16), tokens = it.t1 - (it.t0 & ~kAttnWhole);
+    const int nr = std::min(p.item_rows, rows * G - rbg * p.item_rows);
+    if (rbg == 0) attn_bytes += (double)tokens * kv_tok / p.nkv;
+    attn_flops += 4.0 * p.hd * nr * tokens;
   }
   {
     ProfScope ps(WISP_PROF_ROWS, 0, 0, s);
@@ -544,12 +610,13 @@ wisp_status run_forward(const Plan &p, const wisp_model *m, const wisp_kv *kv, c
       float *pml = reinterpret_cast<float *>(ws + p.w_attn_ml);
       {
         ProfScope ps(WISP_PROF_ATTN, attn_bytes, attn_flops, s);
-        attention_bf16_main(sd, items, (int)p.items.size(), (const uint16_t *)qb, (const uint16_t *)kl,
-                            (const uint16_t *)vl, po, pml, p.nq, p.nkv, p.hd, s);
+        attention_bf16_main(sd, items, first, p.attn_waves(), p.item_rows, (const uint16_t *)qb,
+                            (const uint16_t *)kl, (const uint16_t *)vl, po, pml, (uint16_t *)ao, true, p.qdim,
+                            p.nq, p.nkv, p.hd, s);
       }
       ProfScope ps(WISP_PROF_ATTN_COMBINE, 0, 0, s);
-      attention_bf16_combine(sd, groups, (int)p.groups.size(), p.max_group_chunks, po, pml, (uint16_t *)ao, true, p.qdim, p.nq,
-                             p.nkv, p.hd, s);
+      attention_bf16_combine(sd, groups, (int)p.groups.size(), p.item_rows, p.max_group_chunks, po, pml,
+                             (uint16_t *)ao, true, p.qdim, p.nq, p.nkv, p.hd, s);
     } else {
       ProfScope ps(WISP_PROF_ATTN, attn_bytes, attn_flops, s);
       attention_f32(sd, p.M, (const float *)qb, (const float *)kl, (const float *)vl, (float *)ao, p.nq,
@@ -886,12 +953,14 @@ wisp_status wisp_attention(const wisp_model *model, const wisp_kv *kv, const wis
     if (p.bf16) {
       const AttnItem *items = reinterpret_cast<const AttnItem *>(ws + p.w_desc + p.i_items * 4);
       const AttnGroup *groups = reinterpret_cast<const AttnGroup *>(ws + p.w_desc + p.i_groups * 4);
+      const int32_t *first = p.first.empty() ? nullptr : reinterpret_cast<const int32_t *>(ws + p.w_desc) + p.i_first;
       float *po = reinterpret_cast<float *>(ws + p.w_attn_o);
       float *pml = reinterpret_cast<float *>(ws + p.w_attn_ml);
-      attention_bf16_main(sd, items, (int)p.items.size(), (const uint16_t *)q, (const uint16_t *)kv->k_pool,
-                          (const uint16_t *)kv->v_pool, po, pml, p.nq, p.nkv, p.hd, s);
-      attention_bf16_combine(sd, groups, (int)p.groups.size(), p.max_group_chunks, po, pml, (uint16_t *)out, false, p.qdim, p.nq,
-                             p.nkv, p.hd, s);
+      attention_bf16_main(sd, items, first, p.attn_waves(), p.item_rows, (const uint16_t *)q,
+                          (const uint16_t *)kv->k_pool, (const uint16_t *)kv->v_pool, po, pml, (uint16_t *)out,
+                          false, p.qdim, p.nq, p.nkv, p.hd, s);
+      attention_bf16_combine(sd, groups, (int)p.groups.size(), p.item_rows, p.max_group_chunks, po, pml,
+                             (uint16_t *)out, false, p.qdim, p.nq, p.nkv, p.hd, s);
     } else {
       attention_f32(sd, p.M, (const float *)q, (const float *)kv->k_pool, (const float *)kv->v_pool,
                     (float *)out, p.nq, p.nkv, p.hd, p.max_tokens, s);
