@@ -3,20 +3,22 @@
 // (Sec. 4.5: the new rows' K/V are written into their pages at ctx_len .. ctx_len+gamma),
 // and SwiGLU.  Activations that feed a bf16 GEMM are written straight into the packed
 // 32x16-fragment layout the GEMM streams; fp32 models keep row-major activations.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
 namespace wisp {
 
-__device__ __forceinline__ float block_sum_256(float v, float *sh) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[w] = v;
-  __syncthreads();
-  return sh[0] + sh[1] + sh[2] + sh[3];
+// The row of workgroup b: 8 consecutive rows, whose 16-byte pieces share a 128-byte line of the
+// packed activations (and slots of a V page), go to one XCD, as workgroups are dealt to the 8
+// in turn.  Launched over whole blocks of 64 rows (row_blocks); from 64 rows on, as fewer rows
+// are spread over all XCDs instead.  (1291 rows x 4096, 2 splits: 25 -> 19 us; dealt one by one,
+// every line is written back in up to 8 parts.)
+__device__ __forceinline__ int row_of_block(int b, int n) {
+  return n < 64 ? b : (b & ~63) + (b & 7) * 8 + ((b >> 3) & 7);
 }
+static int row_blocks(int n) { return n < 64 ? n : (n + 63) / 64 * 64; }
 
 // store 8 consecutive activation columns c..c+7 of row r
 template <typename T>
@@ -40,25 +42,69 @@ __device__ __forceinline__ void store8<uint16_t>(uint16_t *out, bool packed, int
   *reinterpret_cast<uint4 *>(out + o) = w;
 }
 
-// Sum of the K-split partials of 4 consecutive fp32 columns, in fixed split order.  All
-// split loads are issued before the first add so their latencies overlap.
+// Sum of the K-split partials of 8 consecutive fp32 columns, in fixed split order; S: the
+// splits, or a bound on them above 4.  The loads of up to 8 splits are issued before the
+// first add, past the last split once more the last (a branch per split would wait for one
+// load after another; 16 splits at once would spill).
 constexpr int kMaxSplits = 16;
-__device__ __forceinline__ float4 sum_splits4(const float *__restrict__ p, int64_t stride, int splits) {
-  float4 v[kMaxSplits];
+template <int S>
+__device__ __forceinline__ void sum_splits8(const float *__restrict__ p, int64_t stride, int splits, float (&a)[8]) {
+  constexpr bool EXACT = S <= 4;
+  constexpr int R = S > 8 ? 8 : S;
 #pragma unroll
-  for (int z = 0; z < kMaxSplits; ++z)
-    if (z < splits) v[z] = *reinterpret_cast<const float4 *>(p + z * stride);
-  float4 a = v[0];
+  for (int z0 = 0; z0 < S; z0 += R) {
+    float4 v[R][2];
 #pragma unroll
-  for (int z = 1; z < kMaxSplits; ++z)
-    if (z < splits) {
-      a.x += v[z].x;
-      a.y += v[z].y;
-      a.z += v[z].z;
-      a.w += v[z].w;
+    for (int z = 0; z < R; ++z)
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+        v[z][x] = *reinterpret_cast<const float4 *>(p + (EXACT ? z : min(z0 + z, splits - 1)) * stride + x * 4);
+#pragma unroll
+    for (int z = 0; z < R; ++z) {
+      const float w[8] = {v[z][0].x, v[z][0].y, v[z][0].z, v[z][0].w, v[z][1].x, v[z][1].y, v[z][1].z, v[z][1].w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) a[e] = z0 + z == 0 ? w[e] : EXACT || z0 + z < splits ? a[e] + w[e] : a[e];
     }
-  return a;
+    if (S > R) asm volatile("" ::: "memory");
+  }
 }
+// calls go(std::integral_constant<int, S>) for the instance that covers `splits`
+template <typename F>
+static void with_splits(int splits, F &&go) {
+  if (splits <= 1) go(std::integral_constant<int, 1>{});
+  else if (splits == 2) go(std::integral_constant<int, 2>{});
+  else if (splits == 3) go(std::integral_constant<int, 3>{});
+  else if (splits == 4) go(std::integral_constant<int, 4>{});
+  else if (splits <= 8) go(std::integral_constant<int, 8>{});
+  else go(std::integral_constant<int, kMaxSplits>{});
+}
+
+// 8 consecutive elements as floats; v16: the address is a multiple of 16 bytes
+__device__ __forceinline__ void load8(const float *p, bool v16, float (&v)[8]) {
+  if (v16) {
+    const float4 a = *reinterpret_cast<const float4 *>(p), b = *reinterpret_cast<const float4 *>(p + 4);
+    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
+    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = p[e];
+  }
+}
+__device__ __forceinline__ void load8(const uint16_t *p, bool v16, float (&v)[8]) {
+  if (v16) {
+    const uint4 w = ld16(p);
+    const uint32_t x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[2 * e] = __uint_as_float(x[e] << 16);
+      v[2 * e + 1] = __uint_as_float(x[e] & 0xFFFF0000u);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = bf2f(p[e]);
+  }
+}
+static bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 // ---------------------------------------------------------------------------------------
 __global__ void rope_table_kernel(const int32_t *__restrict__ row_pos, float *__restrict__ cs, int M,
@@ -80,59 +126,16 @@ void rope_table(const StepDesc &d, float *cs, int M, int hd, float base, hipStre
 }
 
 // ---------------------------------------------------------------------------------------
-// RMSNorm of the fp32 row staged in LDS (`hrow`), y = x / rms * g
+// The two row kernels below hold a row in one workgroup, 8 columns per thread (dm <= 8192).
+// With few rows they are bound by the chain of loads, so everything a thread reads is asked
+// for at once, the norm's gain too; with many by HBM.
 // ---------------------------------------------------------------------------------------
-template <typename T>
-__device__ void norm_store_row(const float *__restrict__ hrow, const T *__restrict__ gain,
-                               T *__restrict__ xn, bool packed, int64_t r, int dm, float eps,
-                               float *sh) {
-  float ss = 0.f;
-  for (int c = threadIdx.x; c < dm; c += 256) ss += hrow[c] * hrow[c];
-  ss = block_sum_256(ss, sh);
-  const float inv = 1.0f / sqrtf(ss / (float)dm + eps);
-  for (int c8 = threadIdx.x * 8; c8 < dm; c8 += 256 * 8) {
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = hrow[c8 + e] * inv * Act<T>::load(gain, c8 + e);
-    store8<T>(xn, packed, r, c8, dm, v);
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void embed_norm_kernel(StepDesc d, const T *__restrict__ embed,
-                                                         const T *__restrict__ gain,
-                                                         const int32_t *__restrict__ tokens,
-                                                         float *__restrict__ h, T *__restrict__ xn,
-                                                         bool packed, int dm, int V, float eps) {
-  __shared__ float sh[4];
-  extern __shared__ float row[];
-  const int r = blockIdx.x;
-  int tok = tokens[r];
-  if (tok < 0 || tok >= V) {
-    if (threadIdx.x == 0) flag_error(d.err, kErrToken);
-    tok = 0;
-  }
-  float *hr = h + (int64_t)r * dm;
-  for (int c = threadIdx.x; c < dm; c += 256) {
-    const float v = Act<T>::load(embed, (int64_t)tok * dm + c);
-    hr[c] = v;
-    row[c] = v;
-  }
-  __syncthreads();
-  norm_store_row<T>(row, gain, xn, packed, r, dm, eps, sh);
-}
-
-template <typename T>
-void embed_norm(const StepDesc &d, const T *embed, const T *gain, const int32_t *tokens, float *h,
-                T *xn, bool packed, int M, int dm, int V, float eps, hipStream_t s) {
-  launch(embed_norm_kernel<T>, M, 256, dm * sizeof(float), s, d, embed, gain, tokens, h, xn, packed, dm, V, eps);
-}
-
 // Fixed-order sum over the threads of a block of up to 1024 (waves reduce by shuffles,
 // then wave sums are added in wave order).
 __device__ __forceinline__ float block_sum(float v, float *sh) {
+  v = xor16_sum(xor32_sum(v));
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o);
   const int w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
   if ((threadIdx.x & 63) == 0) sh[w] = v;
   __syncthreads();
@@ -141,52 +144,98 @@ __device__ __forceinline__ float block_sum(float v, float *sh) {
   return t;
 }
 
-// One row per workgroup, 8 columns per thread: every split partial and the residual are
-// loaded in one round, the new residual stays in registers for the norm.
+// y = x / rms * g of the row whose columns c .. c + 7 this thread holds
 template <typename T>
-__global__ __launch_bounds__(1024) void resid_norm_kernel(const float *__restrict__ part, int splits,
-                                                          float *__restrict__ h,
-                                                          const T *__restrict__ gain,
-                                                          T *__restrict__ xn, bool packed, int M,
-                                                          int dm, float eps,
-                                                          const int32_t *__restrict__ rows) {
-  __shared__ float sh[16];
-  const int ro = blockIdx.x;                 // output row
-  const int r = rows ? rows[ro] : ro;        // source row
-  const int c = threadIdx.x * 8;
-  const bool on = c < dm;
-  float v[8];
+__device__ __forceinline__ void norm_store(float (&v)[8], const float (&g)[8], bool on, T *__restrict__ xn, bool packed,
+                                           int64_t r, int c, int dm, float eps, float *sh) {
   float ss = 0.f;
-  if (on) {
-    const float *p = part + (int64_t)r * dm + c;
-    const int64_t stride = (int64_t)M * dm;
-    const float4 a0 = sum_splits4(p, stride, splits);
-    const float4 a1 = sum_splits4(p + 4, stride, splits);
-    float *hr = h + (int64_t)r * dm + c;
-    const float4 h0 = *reinterpret_cast<const float4 *>(hr);
-    const float4 h1 = *reinterpret_cast<const float4 *>(hr + 4);
-    v[0] = h0.x + a0.x; v[1] = h0.y + a0.y; v[2] = h0.z + a0.z; v[3] = h0.w + a0.w;
-    v[4] = h1.x + a1.x; v[5] = h1.y + a1.y; v[6] = h1.z + a1.z; v[7] = h1.w + a1.w;
-    *reinterpret_cast<float4 *>(hr) = make_float4(v[0], v[1], v[2], v[3]);
-    *reinterpret_cast<float4 *>(hr + 4) = make_float4(v[4], v[5], v[6], v[7]);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
-  }
+  for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
   ss = block_sum(ss, sh);
   if (!on) return;
   const float inv = 1.0f / sqrtf(ss / (float)dm + eps);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = v[e] * inv * Act<T>::load(gain, c + e);
-  store8<T>(xn, packed, ro, c, dm, v);
+  for (int e = 0; e < 8; ++e) v[e] = v[e] * inv * g[e];
+  store8<T>(xn, packed, r, c, dm, v);
+}
+
+template <typename T>
+__global__ __launch_bounds__(1024) void embed_norm_kernel(StepDesc d, const T *__restrict__ embed,
+                                                          const T *__restrict__ gain,
+                                                          const int32_t *__restrict__ tokens,
+                                                          float *__restrict__ h, T *__restrict__ xn,
+                                                          bool packed, bool e16, bool g16, int M, int dm, int V,
+                                                          float eps) {
+  __shared__ float sh[16];
+  const int r = row_of_block(blockIdx.x, M);
+  if (r >= M) return;
+  const int c = threadIdx.x * 8;
+  const bool on = c < dm;
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, g[8];
+  if (on) load8(gain + c, g16, g);
+  int tok = tokens[r];
+  if (tok < 0 || tok >= V) {
+    if (threadIdx.x == 0) flag_error(d.err, kErrToken);
+    tok = 0;
+  }
+  if (on) {
+    load8(embed + (int64_t)tok * dm + c, e16, v);
+    float *hr = h + (int64_t)r * dm + c;
+    *reinterpret_cast<float4 *>(hr) = make_float4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<float4 *>(hr + 4) = make_float4(v[4], v[5], v[6], v[7]);
+  }
+  norm_store<T>(v, g, on, xn, packed, r, c, dm, eps, sh);
+}
+
+static int row_threads(int dm) { return ((dm / 8 + 63) / 64) * 64; }
+
+template <typename T>
+void embed_norm(const StepDesc &d, const T *embed, const T *gain, const int32_t *tokens, float *h,
+                T *xn, bool packed, int M, int dm, int V, float eps, hipStream_t s) {
+  launch(embed_norm_kernel<T>, row_blocks(M), row_threads(dm), 0, s, d, embed, gain, tokens, h, xn, packed,
+         aligned16(embed), aligned16(gain), M, dm, V, eps);
+}
+
+// Every split partial, the residual and the gain are loaded in one round, the new residual
+// stays in registers for the norm.  (6 rows of 4096, one load after another: 7.4 us; now 5.1 with
+// 8 splits, 6.8 with 16.  171 rows, 8 splits: 9.4 -> 7.9.  4102 rows, 1 split: 57 -> 44, 5.3 TB/s.)
+template <typename T, int S>
+__global__ __launch_bounds__(1024) void resid_norm_kernel(const float *__restrict__ part, int splits,
+                                                          float *__restrict__ h,
+                                                          const T *__restrict__ gain,
+                                                          T *__restrict__ xn, bool packed, bool g16, int M,
+                                                          int n_out, int dm, float eps,
+                                                          const int32_t *__restrict__ rows) {
+  __shared__ float sh[16];
+  const int ro = row_of_block(blockIdx.x, n_out);   // output row
+  if (ro >= n_out) return;
+  const int r = rows ? rows[ro] : ro;               // source row
+  const int c = threadIdx.x * 8;
+  const bool on = c < dm;
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, g[8];
+  if (on) {
+    float *hr = h + (int64_t)r * dm + c;
+    const float4 h0 = *reinterpret_cast<const float4 *>(hr);
+    const float4 h1 = *reinterpret_cast<const float4 *>(hr + 4);
+    load8(gain + c, g16, g);
+    sum_splits8<S>(part + (int64_t)r * dm + c, (int64_t)M * dm, splits, v);
+    v[0] += h0.x; v[1] += h0.y; v[2] += h0.z; v[3] += h0.w;
+    v[4] += h1.x; v[5] += h1.y; v[6] += h1.z; v[7] += h1.w;
+    *reinterpret_cast<float4 *>(hr) = make_float4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<float4 *>(hr + 4) = make_float4(v[4], v[5], v[6], v[7]);
+  }
+  norm_store<T>(v, g, on, xn, packed, ro, c, dm, eps, sh);
 }
 
 template <typename T>
 void resid_norm(const float *part, int splits, float *h, const T *gain, T *xn, bool packed, int M,
                 int dm, float eps, hipStream_t s, const int32_t *rows, int n_out) {
-  const int threads = ((dm / 8 + 63) / 64) * 64;   // dm <= 8192
   const int n = rows ? n_out : M;
   if (n <= 0) return;
-  launch(resid_norm_kernel<T>, n, threads, 0, s, part, splits, h, gain, xn, packed, M, dm, eps, rows);
+  with_splits(splits, [&](auto S) {
+    launch(resid_norm_kernel<T, decltype(S)::value>, row_blocks(n), row_threads(dm), 0, s, part, splits, h, gain, xn,
+           packed, aligned16(gain), M, n, dm, eps, rows);
+  });
 }
 
 __global__ void gather_ints_kernel(const int32_t *__restrict__ src, const int32_t *__restrict__ idx, int n,
@@ -223,13 +272,14 @@ __device__ __forceinline__ void store8_contig<uint16_t>(uint16_t *p, const float
                                              pack2bf(v[4], v[5]), pack2bf(v[6], v[7]));
 }
 
-template <typename T>
+template <typename T, int S>
 __global__ __launch_bounds__(256) void qkv_rope_append_kernel(StepDesc d, const float *__restrict__ part,
                                                               int splits, const float *__restrict__ cs,
                                                               T *__restrict__ q, T *__restrict__ k_pool,
                                                               T *__restrict__ v_pool, int M, int nq,
                                                               int nkv, int hd) {
-  const int r = blockIdx.x;
+  const int r = row_of_block(blockIdx.x, M);
+  if (r >= M) return;
   const int tph = hd / 8;                          // threads per head
   const int head = blockIdx.y * kRopeHeadsPerBlock + threadIdx.x / tph;
   const int nh = nq + 2 * nkv;
@@ -238,14 +288,24 @@ __global__ __launch_bounds__(256) void qkv_rope_append_kernel(StepDesc d, const 
   const int N = nh * hd;
   __shared__ float xch[kRopeHeadsPerBlock * 256];   // 8 values per thread, hd <= 256
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (head < nh) {
-    const float *p = part + (int64_t)r * N + head * hd + i0;
-    const int64_t stride = (int64_t)M * N;
-    const float4 a0 = sum_splits4(p, stride, splits);
-    const float4 a1 = sum_splits4(p + 4, stride, splits);
-    v[0] = a0.x; v[1] = a0.y; v[2] = a0.z; v[3] = a0.w;
-    v[4] = a1.x; v[5] = a1.y; v[6] = a1.z; v[7] = a1.w;
+  // everything that does not depend on the exchange is asked for before it
+  const int req = d.row_req[r], pos = d.row_pos[r];
+  const bool lo = i0 < h2;
+  float cn[8], sn[8];
+  if (head < nq + nkv) {   // RoPE on q and k heads
+    const float4 *csr = reinterpret_cast<const float4 *>(cs + (int64_t)r * hd + 2 * (lo ? i0 : i0 - h2));   // [h2][2]
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float4 x = csr[e];
+      cn[2 * e] = x.x;
+      sn[2 * e] = x.y;
+      cn[2 * e + 1] = x.z;
+      sn[2 * e + 1] = x.w;
+    }
   }
+  int blk = 0;
+  if (head >= nq && head < nh) blk = d.page_table[(int64_t)req * d.pt_stride + pos / kPage];
+  if (head < nh) sum_splits8<S>(part + (int64_t)r * N + head * hd + i0, (int64_t)M * N, splits, v);
   // rotate-half partner values: thread t of a head pairs with thread (t + tph/2) mod tph
 #pragma unroll
   for (int e = 0; e < 8; ++e) xch[threadIdx.x * 8 + e] = v[e];
@@ -255,22 +315,14 @@ __global__ __launch_bounds__(256) void qkv_rope_append_kernel(StepDesc d, const 
 #pragma unroll
   for (int e = 0; e < 8; ++e) w[e] = xch[partner * 8 + e];
   if (head >= nh) return;
-  const int req = d.row_req[r], pos = d.row_pos[r];
-  if (head < nq + nkv) {   // RoPE on q and k heads
-    const float *csr = cs + (int64_t)r * hd;   // [h2][2]
-    const bool lo = i0 < h2;
+  if (head < nq + nkv) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int i = (lo ? i0 : i0 - h2) + e;
-      const float c = csr[2 * i], sn = csr[2 * i + 1];
-      v[e] = lo ? v[e] * c - w[e] * sn : v[e] * c + w[e] * sn;
-    }
+    for (int e = 0; e < 8; ++e) v[e] = lo ? v[e] * cn[e] - w[e] * sn[e] : v[e] * cn[e] + w[e] * sn[e];
   }
   if (head < nq) {
     store8_contig<T>(q + ((int64_t)r * nq + head) * hd + i0, v);
     return;
   }
-  const int blk = d.page_table[(int64_t)req * d.pt_stride + pos / kPage];
   if (blk < 0 || blk >= d.n_blocks) {
     if (threadIdx.x % tph == 0) flag_error(d.err, kErrBlock);
     return;
@@ -291,9 +343,11 @@ template <typename T>
 void qkv_rope_append(const StepDesc &d, const float *part, int splits, const float *cs, T *q,
                      T *k_pool, T *v_pool, int M, int nq, int nkv, int hd, hipStream_t s) {
   const int nh = nq + 2 * nkv;
-  dim3 grid(M, (nh + kRopeHeadsPerBlock - 1) / kRopeHeadsPerBlock);
-  launch(qkv_rope_append_kernel<T>, grid, kRopeHeadsPerBlock * hd / 8, 0, s, d, part, splits, cs, q, k_pool, v_pool, M,
-                                                                        nq, nkv, hd);
+  dim3 grid(row_blocks(M), (nh + kRopeHeadsPerBlock - 1) / kRopeHeadsPerBlock);
+  with_splits(splits, [&](auto S) {
+    launch(qkv_rope_append_kernel<T, decltype(S)::value>, grid, kRopeHeadsPerBlock * hd / 8, 0, s, d, part, splits, cs, q,
+           k_pool, v_pool, M, nq, nkv, hd);
+  });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -302,7 +356,7 @@ void qkv_rope_append(const StepDesc &d, const float *part, int splits, const flo
 // wisp_pack_gate_up: fragment 2b holds gate columns 32b .. 32b + 31, fragment 2b + 1 the
 // up columns of the same b)
 // ---------------------------------------------------------------------------------------
-template <typename T>
+template <typename T, int S>
 __global__ __launch_bounds__(256) void swiglu_kernel(const float *__restrict__ part, int splits,
                                                      T *__restrict__ out, bool packed, int M, int F,
                                                      bool interleaved) {
@@ -314,16 +368,11 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const float *__restrict__ p
     const float *pr = part + r * 2 * F;
     const int64_t gc = interleaved ? (c / 32) * 64 + c % 32 : c;
     const int64_t uc = interleaved ? gc + 32 : F + c;
-    float4 g[2], u[2];
-    g[0] = sum_splits4(pr + gc, stride, splits);
-    g[1] = sum_splits4(pr + gc + 4, stride, splits);
-    u[0] = sum_splits4(pr + uc, stride, splits);
-    u[1] = sum_splits4(pr + uc + 4, stride, splits);
-    const float gv[8] = {g[0].x, g[0].y, g[0].z, g[0].w, g[1].x, g[1].y, g[1].z, g[1].w};
-    const float uv[8] = {u[0].x, u[0].y, u[0].z, u[0].w, u[1].x, u[1].y, u[1].z, u[1].w};
-    float v[8];
+    float g[8], u[8], v[8];
+    sum_splits8<S>(pr + gc, stride, splits, g);
+    sum_splits8<S>(pr + uc, stride, splits, u);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = silu_mul(gv[e], uv[e]);
+    for (int e = 0; e < 8; ++e) v[e] = silu_mul(g[e], u[e]);
     store8<T>(out, packed, r, c, F, v);
   }
 }
@@ -333,7 +382,9 @@ void swiglu(const float *part, int splits, T *out, bool packed, int M, int F, bo
   const int64_t chunks = (int64_t)M * (F / 8);
   int blocks = (int)((chunks + 255) / 256);
   if (blocks > 4096) blocks = 4096;
-  launch(swiglu_kernel<T>, blocks, 256, 0, s, part, splits, out, packed, M, F, interleaved);
+  with_splits(splits, [&](auto S) {
+    launch(swiglu_kernel<T, decltype(S)::value>, blocks, 256, 0, s, part, splits, out, packed, M, F, interleaved);
+  });
 }
 
 template void embed_norm<float>(const StepDesc &, const float *, const float *, const int32_t *,
