@@ -194,21 +194,24 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
       for (int g = 0, m = row_groups(i, R); g < m; ++g) n += p.nkv * ((group_pairs(i, g, R) + L - 1) / L);
     return n;
   };
-  // One item per wave while that takes items of at most 16 pairs: a group's pairs cut into equal
-  // parts of at most L, L the shortest whose items fit one wave per SIMD or, with 32 rows, two.
+  // One item per wave where items of at most 16 pairs (32 with 48 or 64 rows, which have no
+  // second wave per SIMD) fit one wave per SIMD: a group's pairs cut into equal parts of at most
+  // L, the shortest that fits; or, with 32 rows, where items of 16 pairs fit two per SIMD.
   // (Two on some SIMDs only are slower than one on each: 32 requests of 0.5-2k 30 us per layer
-  // in 1008 items, 38 in 1200; 64 of 0.5-4k 85 us in 2032, 106 in 1032.)  If 16 pairs do not
-  // fit, the groups themselves are many, and the left-over workgroups start as others end.
+  // in 1008 items, 38 in 1200; 64 of 0.5-4k 85 us in 2032, 106 in 1032.  48 rows: 22 of 3-4.5k
+  // 63 us in 912 items of 24 pairs, 66 in shares.)  If the groups themselves are more, the
+  // left-over workgroups start as others end.
   // Beyond that, equal shares of all pairs per wave (64 of 0.5-4k, 14 pairs per wave: 91
   // instead of 85 us; 4 prompts of 512: 55 instead of 43; 256 of 1-8k, 110 per wave: 610
-  // instead of 692).
+  // instead of 692; 48 rows, 64 of 0.5-4k: 90, against 118 in 1040 items).
   constexpr int64_t kShort = 16;
-  const bool few = total <= kShort * slots && count_items(kShort) <= slots;
+  const int64_t one_round = R == 32 ? kShort : 2 * kShort;
+  const bool few = total <= one_round * slots && count_items(one_round) <= slots;
   const int64_t waves = std::max<int64_t>(1, std::min(R == 32 && !few ? 2 * slots : slots, total));
-  const bool single = total <= kShort * waves;
+  const bool single = few || total <= kShort * waves;
   int64_t L = std::max<int64_t>(2, (total + waves - 1) / waves);
   if (single)
-    while (L < kShort && count_items(L) > waves) ++L;
+    while (L < (few ? one_round : kShort) && count_items(L) > waves) ++L;
   if (few) {
     // Small batches leave wave slots idle even at the shortest items, and their step is
     // latency-bound: longer items then cost little, while a group of more than
