@@ -9,6 +9,7 @@
 // to about 315 rows; K is split across workgroups when there are too few output tiles to
 // fill the 256 CUs, and the fp32 partial sums are added in a fixed order by the consuming
 // epilogue kernel.  Larger row counts take the tiles of gemm_tile.hip.
+#include <stdexcept>
 #include <type_traits>
 
 #include "common.h"
@@ -206,10 +207,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_ring_kernel(const uint16_t 
 }
 
 static constexpr int kNarrowAD = 1;   // activation prefetch depth of the 32-column ring
+// most row fragments of a workgroup of the 32- and the 64-column ring (launch_ring's instances)
+static constexpr int kRingMaxMT1 = 2, kRingMaxMT2 = 5;
 
 // Launch plan.  LDS-staged output tiles (gemm_tile.hip) for most shapes, the weight ring
-// (above) where it streams faster or K does not fit the tile's chunks (at most 64 rows and K
-// not a multiple of 64).  Tile variant by
+// (above) where it streams faster or K does not fit the tile's chunks (64 columns up to 64
+// rows, 32 beyond; every K of a model is a multiple of 32).  Tile variant by
 // row fragments, measured with cold weights on the 8B and 70B projections at 7-4108 rows:
 //   1 (<= 32 rows): the 32 x 256 tile with up to 16 K splits for projections of >= 20M
 //     weights (at 7 rows QKV 13.4 -> 11.5 us, down 24.0 -> 20.1, LM head 169.5 -> 158.9);
@@ -235,8 +238,10 @@ static constexpr int kNarrowAD = 1;   // activation prefetch depth of the 32-col
 // us alone, the 70B step 76.9 -> 75.8 ms; QKV of 48 tiles on 5: 8B at 100 rows 16.5 -> 14.9 us
 // alone, the 8B step at 171 rows unchanged, the extra partial costing the row kernels what it
 // saves).
-// The ring holds all rows (at most 160 reach it): 64-column wave tiles for wide outputs,
-// 32-column tiles with a deeper ring otherwise; K split for one resident round.
+// The ring: 64-column wave tiles for wide outputs, 32-column tiles with a deeper ring
+// otherwise, every row in one block (a model has at most 5 row fragments there on wide outputs
+// and 2 otherwise; more, which only a K of 16 mod 32 brings, in several blocks of that
+// size); K split for one resident round.
 static constexpr int kRound = 256;        // workgroups resident at once (one per CU)
 static constexpr int kWideTiles = 224;    // 7/8 of a round
 // measured time of one 32-column chunk of a full round of 256-column tiles, and what a round
@@ -272,7 +277,7 @@ GemmCfg gemm_bf16_plan(int M, int N, int K) {
   else if (mf == 6) variant = fills ? 4 : 1;
   else if (mf <= 8) variant = fills ? 17 : 13;
   else if (mf <= 12) variant = 4;
-  else {
+  else if (K % 32 == 0) {
     auto us = [&](int v, const TileUs &u) {
       const TileShape ts = tile_shape(v);
       const int tiles = tile_count(mf, N, ts);
@@ -281,7 +286,7 @@ GemmCfg gemm_bf16_plan(int M, int N, int K) {
       return (double)((tiles * (int64_t)s + kRound - 1) / kRound) * (kcs * u.chunk + u.round);
     };
     variant = us(4, kTileUs192) < 0.875 * us(17, kTileUs256) ? 4 : 17;
-  }
+  } else variant = 0;
   if (variant) {
     const TileShape ts = tile_shape(variant);
     if (K % (16 * ts.ks) == 0) {
@@ -299,14 +304,14 @@ GemmCfg gemm_bf16_plan(int M, int N, int K) {
       return c;
     }
   }
-  // every row in one block (at most 5 fragments reach the ring)
-  c.rb = 1;
   c.kind = N >= 16384 ? 2 : 1;
-  c.mt = mf;
-  c.bm = 32 * mf;
+  const int mt_max = c.kind == 2 ? kRingMaxMT2 : kRingMaxMT1;
+  c.rb = (mf + mt_max - 1) / mt_max;
+  c.mt = (mf + c.rb - 1) / c.rb;
+  c.bm = 32 * c.mt;
   c.bn = c.kind == 2 ? 256 : 128;
   const int R = c.kind == 2 ? 4 : 8;
-  const int tiles = (N + c.bn - 1) / c.bn;
+  const int tiles = (N + c.bn - 1) / c.bn * c.rb;
   // workgroups resident at once: the ring kernels hold one workgroup per CU (LDS and
   // registers), so more than one round of 256 would leave a partial second round
   const int max_wg = 256;
@@ -319,18 +324,15 @@ GemmCfg gemm_bf16_plan(int M, int N, int K) {
   return c;
 }
 
-template <int NT, int R, int AD>
+template <int NT, int R, int AD, int MAX_MT>
 static void launch_ring(int mt, dim3 grid, const uint16_t *A, const uint16_t *W, float *C, int M,
                         int N, int K, int ldc, int kps, hipStream_t s) {
-  switch (mt) {
-#define WISP_RING_CASE(X) \
-  case X: launch(gemm_ring_kernel<1, 4, X, NT, R, AD>, grid, 256, 0, s, A, W, C, M, N, K, ldc, kps); break;
-    WISP_RING_CASE(1)
-    WISP_RING_CASE(2)
-    WISP_RING_CASE(3)
-    WISP_RING_CASE(4)
-    WISP_RING_CASE(5)
-#undef WISP_RING_CASE
+  if constexpr (MAX_MT == 0) {
+    throw std::logic_error("gemm_bf16: no ring kernel for the plan's row fragments");
+  } else if (mt == MAX_MT) {
+    launch(gemm_ring_kernel<1, 4, MAX_MT, NT, R, AD>, grid, 256, 0, s, A, W, C, M, N, K, ldc, kps);
+  } else {
+    launch_ring<NT, R, AD, MAX_MT - 1>(mt, grid, A, W, C, M, N, K, ldc, kps, s);
   }
 }
 
@@ -342,9 +344,9 @@ void gemm_bf16(const uint16_t *A, const uint16_t *W, float *C, int M, int N, int
   }
   dim3 grid(((N + cfg.bn - 1) / cfg.bn) * cfg.splits, cfg.rb, 1);
   if (cfg.kind == 1)
-    launch_ring<1, 8, kNarrowAD>(cfg.mt, grid, A, W, C, M, N, K, ldc, cfg.kf_per_split, s);
+    launch_ring<1, 8, kNarrowAD, kRingMaxMT1>(cfg.mt, grid, A, W, C, M, N, K, ldc, cfg.kf_per_split, s);
   else
-    launch_ring<2, 4, 2>(cfg.mt, grid, A, W, C, M, N, K, ldc, cfg.kf_per_split, s);
+    launch_ring<2, 4, 2, kRingMaxMT2>(cfg.mt, grid, A, W, C, M, N, K, ldc, cfg.kf_per_split, s);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -233,6 +233,20 @@ def test_gemm_plan_of_the_wide_projections(W):
         W.gemm_plan(0, 1024, 256)
 
 
+@pytest.mark.parametrize("M", [7, 33, 65, 160, 161, 200, 300, 400, 1000, 4108])
+def test_gemm_plan_of_every_accepted_k(W, M):
+    """wisp_gemm_plan takes any K that is a multiple of 16, also those no model has (16 mod
+    32): every plan names a launch that exists (the rings hold at most 2 row fragments of
+    32-column tiles or 5 of 64-column tiles), covers all rows and leaves no K range empty."""
+    for N in (32, 4096, 28672, 65536):
+        for K in (16, 32, 48, 80, 112, 4112, 4128):
+            t = W.gemm_plan(M, N, K)
+            assert t["kind"] in (1, 2, 4), (N, K, t)
+            assert t["rb"] * t["mt"] * 32 >= M and t["rb"] >= 1 and 1 <= t["splits"] <= max(1, K // 16), (N, K, t)
+            if t["kind"] != 4:
+                assert t["mt"] <= (5 if t["kind"] == 2 else 2), (N, K, t)
+
+
 def test_noalloc_rejects_batches_beyond_its_static_scratch(W):
     """wisp_verify_noalloc refuses a batch whose scratch exceeds WISP_NOALLOC_SCRATCH_BYTES
     with WISP_E_WORKSPACE, before any GPU work (fake device pointers are never touched)."""
