@@ -287,10 +287,9 @@ wisp_status wisp_profile_reset(void);
 /*
  * Launch plan of one bf16 projection of the step (host only; introspection for tests and
  * benchmarks): M rows, N output columns, K inputs.  out[0] = kernel variant (1: 32-column
- * weight ring, 2: 64-column weight ring, 4: LDS-staged output tiles), out[1] = row blocks,
- * out[2] = 32-row fragments per row block (a block of 12 is two row tiles of 192 rows, any
- * other block one row tile), out[3] = K ranges whose fp32 partial sums are added in fixed
- * order.  WISP_E_INVALID for M, N or K < 1, or N and K not multiples of 32 and 16.
+ * weight ring, 2: 64-column weight ring, 4: LDS-staged output tiles), out[1] = row tiles,
+ * out[2] = 32-row fragments per row tile, out[3] = K ranges whose fp32 partial sums are added
+ * in fixed order.  WISP_E_INVALID for M, N or K < 1, or N and K not multiples of 32 and 16.
  */
 wisp_status wisp_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t out[4]);
 

@@ -574,7 +574,7 @@ class KVManager:
 
 
 def gemm_plan(M: int, N: int, K: int) -> dict:
-    """The launch plan of one bf16 projection (wisp_gemm_plan): kernel variant, row blocks,
+    """The launch plan of one bf16 projection (wisp_gemm_plan): kernel variant, row tiles,
     32-row fragments per block, K ranges."""
     out = (C.c_int32 * 4)()
     _ok(lib.wisp_gemm_plan(int(M), int(N), int(K), out))

@@ -296,9 +296,8 @@ GemmCfg gemm_bf16_plan(int M, int N, int K) {
       c.variant = variant;
       c.bm = ts.bm;
       c.bn = ts.bn;
-      // 257-384 rows: one row block, the two row tiles of which run side by side
-      c.rb = mf > 8 && mf <= 12 ? 1 : (mf * 32 + ts.bm - 1) / ts.bm;
-      c.mt = mf > 8 && mf <= 12 ? 12 : ts.bm / 32;
+      c.rb = (mf * 32 + ts.bm - 1) / ts.bm;
+      c.mt = ts.bm / 32;
       c.splits = s;
       c.kf_per_split = kcs * ts.ks;
       return c;

@@ -199,11 +199,12 @@ def test_gemm_plan_of_the_wide_projections(W):
     faster: the output projection at <= 32 rows, the LM head (>= 65536 columns) at 33-160
     rows (64-column wave tiles), small projections at <= 32 rows.  Elsewhere the LDS-staged
     tiles (variant 4) with K split into as many ranges as the work items fit one round of
-    256 workgroups, at most 8 (16 at <= 32 rows), each keeping >= 8 chunks (5 ranges for 48
-    tiles, 3 for 80); at <= 32 rows outputs of 16384-32768 columns on 64-row tiles in one K
-    range; 129-160 rows gate/up on the 192-row tile in one K range; 225-256 rows one 256-row
-    tile, 256 columns wide for the LM head; beyond 384 rows 256 x 256 tiles for every
-    projection."""
+    256 workgroups, at most 8 (16 at <= 32 rows), each keeping the tile's least K columns (128
+    for the 192- and 256-row tiles of 256 columns, 256 for 256 x 128, 512 for the others): 5
+    ranges for 48 tiles, 3 for 80.  At <= 32 rows outputs of 16384-32768 columns on 64-row
+    tiles in one K range; one row tile up to 256 rows (the LM head at 225-256 rows and every
+    output of a round of 256-column tiles 256 columns wide), two of 192 rows at 257-384, and
+    beyond 256-row tiles, or 192-row ones where they take an eighth less time."""
     ring = {  # (M, N, K): kind
         (7, 4096, 4096): 1, (7, 1024, 256): 1, (44, 128256, 4096): 2, (150, 128256, 4096): 2,
         (44, 65536, 512): 2, (153, 65536, 512): 2,
@@ -219,11 +220,12 @@ def test_gemm_plan_of_the_wide_projections(W):
         (150, 28672, 4096): (1, 6, 1), (153, 16384, 512): (1, 6, 1),
         (171, 6144, 4096): (1, 6, 5), (171, 4096, 4096): (1, 6, 8), (171, 28672, 4096): (1, 6, 1),
         (171, 4096, 14336): (1, 6, 8), (171, 128256, 4096): (1, 6, 1),
-        (343, 6144, 4096): (1, 12, 5), (343, 4096, 14336): (1, 12, 8), (343, 28672, 4096): (1, 12, 1),
-        (370, 10240, 8192): (1, 12, 3), (370, 8192, 28672): (1, 12, 4),
+        (343, 6144, 4096): (2, 6, 5), (343, 4096, 14336): (2, 6, 8), (343, 28672, 4096): (2, 6, 1),
+        (370, 10240, 8192): (2, 6, 3), (370, 8192, 28672): (2, 6, 4),
         (476, 16384, 512): (2, 8, 2), (680, 16384, 512): (3, 8, 1), (680, 6144, 4096): (3, 8, 3),
         (680, 4096, 14336): (3, 8, 5), (512, 4096, 4096): (2, 8, 8),
         (1237, 4096, 14336): (5, 8, 3), (1237, 128256, 4096): (5, 8, 1), (1237, 6144, 4096): (5, 8, 2),
+        (1291, 6144, 4096): (7, 6, 1), (1291, 4096, 14336): (7, 6, 2), (96, 57344, 8192): (1, 4, 1),
         (240, 128256, 4096): (1, 8, 1), (240, 28672, 4096): (1, 8, 1), (2108, 1024, 256): (9, 8, 2),
     }
     for (M, N, K), (rb, mt, splits) in tiles.items():
