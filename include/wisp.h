@@ -294,6 +294,19 @@ wisp_status wisp_profile_reset(void);
 wisp_status wisp_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t out[4]);
 
 /*
+ * Work list of one layer's bf16 attention for a batch (host only; introspection for tests and
+ * benchmarks).  A row group is out[0] of a request's rows x query heads of one kv head; its
+ * keys are cut into items.  out[1] = items, out[2] = waves, out[3] = 1 if a wave runs several
+ * items one after another (shares of all keys), 0 if every item has a wave, out[4] = row
+ * groups of more than one item (their partial results are combined), out[5] = most items of
+ * one.  The first max_items items go to `items` (HOST, 8 values each: request, kv head, row
+ * group, first key, end of the keys, 1 if it is its group's only one, wave, 0).  Statuses as
+ * wisp_workspace_size would fail; WISP_E_UNSUPPORTED for an fp32 model.
+ */
+wisp_status wisp_attention_plan(const wisp_model *model, const wisp_batch_desc *desc, int32_t out[6],
+                                int32_t *items, int32_t max_items);
+
+/*
  * Verification batch scheduling (Sec. 4.3, Alg. 1), host code.
  *
  * Batch-time estimator of Sec. 4.4 (seconds):

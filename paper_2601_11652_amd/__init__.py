@@ -44,7 +44,7 @@ EXPORTS = ("wisp_workspace_size", "wisp_logits_workspace_size", "wisp_accept_wor
            "wisp_profile_read", "wisp_profile_reset", "wisp_last_error", "wisp_schedule", "wisp_kvm_create",
            "wisp_kvm_destroy", "wisp_kvm_lookup", "wisp_kvm_reserve", "wisp_kvm_commit", "wisp_kvm_release",
            "wisp_kvm_get_stats", "wisp_draft_stats_workspace_size", "wisp_draft_stats", "wisp_reject_predict",
-           "wisp_gemm_plan", "wisp_verify_noalloc")
+           "wisp_gemm_plan", "wisp_attention_plan", "wisp_verify_noalloc")
 
 
 class WispError(RuntimeError):
@@ -136,6 +136,8 @@ def _load():
     L.wisp_uniform.argtypes = [C.c_uint64, C.c_uint32, C.c_uint32, C.c_uint32, C.c_uint32, _VP, _VP]
     L.wisp_check.argtypes = [_VP, _VP]
     L.wisp_gemm_plan.argtypes = [C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
+    L.wisp_attention_plan.argtypes = [C.POINTER(wisp_model), C.POINTER(wisp_batch_desc), C.POINTER(C.c_int32),
+                                      C.POINTER(C.c_int32), C.c_int32]
     L.wisp_profile_enable.argtypes = [C.c_int]
     L.wisp_profile_read.argtypes = [C.c_int, C.POINTER(C.c_double), C.POINTER(C.c_int64),
                                     C.POINTER(C.c_double), C.POINTER(C.c_double)]
@@ -159,7 +161,7 @@ def _load():
     L.wisp_draft_stats.argtypes = [_VP, C.c_int32, C.c_int32, C.c_int64, C.c_float, _VP, _VP, C.c_size_t, _VP]
     L.wisp_reject_predict.argtypes = [C.POINTER(wisp_reject_mlp), _VP, C.c_int32, _VP, _VP]
     for name in ("wisp_pack_linear", "wisp_pack_gate_up", "wisp_verify", "wisp_verify_noalloc", "wisp_accept", "wisp_attention", "wisp_uniform",
-                 "wisp_check", "wisp_gemm_plan", "wisp_profile_enable", "wisp_profile_read", "wisp_profile_reset",
+                 "wisp_check", "wisp_gemm_plan", "wisp_attention_plan", "wisp_profile_enable", "wisp_profile_read", "wisp_profile_reset",
                  "wisp_schedule", "wisp_kvm_create", "wisp_kvm_lookup", "wisp_kvm_reserve", "wisp_kvm_commit",
                  "wisp_kvm_release", "wisp_kvm_get_stats", "wisp_draft_stats", "wisp_reject_predict"):
         getattr(L, name).restype = C.c_int
@@ -579,6 +581,17 @@ def gemm_plan(M: int, N: int, K: int) -> dict:
     out = (C.c_int32 * 4)()
     _ok(lib.wisp_gemm_plan(int(M), int(N), int(K), out))
     return dict(kind=out[0], rb=out[1], mt=out[2], splits=out[3])
+
+
+def attention_plan(model: wisp_model, desc: "BatchDesc") -> dict:
+    """The work list of one layer's bf16 attention (wisp_attention_plan): rows per row group,
+    waves, whether a wave runs several items, groups to combine, most items of a group, and
+    the items [n][8]: request, kv head, row group, first key, end of the keys, whole, wave, 0."""
+    out = (C.c_int32 * 6)()
+    _ok(lib.wisp_attention_plan(C.byref(model), C.byref(desc.c), out, None, 0))
+    items = np.zeros((out[1], 8), np.int32)
+    _ok(lib.wisp_attention_plan(C.byref(model), C.byref(desc.c), out, items.ctypes.data_as(C.POINTER(C.c_int32)), out[1]))
+    return dict(rows=out[0], waves=out[2], shares=bool(out[3]), combined=out[4], most=out[5], items=items)
 
 
 def wisp_check(workspace, stream=None):

@@ -77,9 +77,9 @@ __global__ __launch_bounds__(256, RB == 2 ? 2 : 1) void attn_bf16_kernel(StepDes
   };
   auto fetched = [&](Item &a) __attribute__((always_inline)) {
     a.req = uni(d0.x);
-    a.kvh = uni(d0.y) & 0xFFFF;
-    a.rbg = (int)((unsigned)uni(d0.y) >> 16);
-    a.t0 = uni(d0.z) & ~kAttnWhole;
+    a.kvh = attn_kvh(uni(d0.y));
+    a.rbg = attn_rbg(uni(d0.y), uni(d0.z));
+    a.t0 = uni(d0.z) & ~kAttnFlags;
     a.whole = uni(d0.z) & kAttnWhole;
     a.t1 = uni(d0.w);
     d_ctx = d.ctx[d0.x];
@@ -384,9 +384,9 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(StepDesc 
   const AttnGroup g = groups[blockIdx.x];
   const int G = nq / nkv;
   const int rows = d.nrow[g.req] * G;
-  const int kvh = g.kvh_rbg & 0xFFFF, lr0 = (int)((unsigned)g.kvh_rbg >> 16) * ROWS;
+  const int n = g.n_items & ~kAttnHighGroup;
+  const int kvh = attn_kvh(g.kvh_rbg), lr0 = attn_rbg(g.kvh_rbg, g.n_items != n ? kAttnHighItem : 0) * ROWS;
   const int nr = min(ROWS, rows - lr0);
-  const int n = g.n_items;
   for (int u = threadIdx.x; u < nr * CH; u += kCombineThreads) {
     const int rr = u / CH, c0 = (u % CH) * 8;   // neighbouring threads: dims of one row
     // partial c of this row; past the last: the last (in range, not used)

@@ -93,14 +93,26 @@ void swiglu(const float *part, int splits, T *out, bool packed, int M, int F, bo
 
 // ----- attention ---------------------------------------------------------------------------
 struct AttnItem {   // a run of one wave's work: request, kv head, row group, token range
-  int32_t req, kvh_rbg, t0, t1;   // t0 a multiple of 32, plus kAttnWhole
+  int32_t req, kvh_rbg, t0, t1;   // kvh_rbg: see attn_pack; t0 a multiple of 32, plus flags
 };
 struct AttnGroup {  // the items (at least two) of one (request, kv head, row group), combined in order
   int32_t req, kvh_rbg, first_item, n_items;
 };
+// A kv head and the low 16 bits of a row group share kvh_rbg; the row group's bit 16 (one
+// request has up to 65570 groups: 32785 rows of 64 query heads per kv head, 32 per group) is
+// bit 1 of an item's t0 and bit 30 of a group's n_items: constants, as scalar registers of the
+// attention kernel are spilled already (a shift by the bits that the heads need cost 6 % at 2
+// requests of 2-8k)
+constexpr int kAttnHighItem = 2, kAttnHighGroup = 1 << 30;
+inline int32_t attn_pack(int kvh, int rbg) { return (int32_t)((uint32_t)rbg << 16 | (uint32_t)kvh); }
+__host__ __device__ inline int attn_kvh(int32_t kvh_rbg) { return kvh_rbg & 0xFFFF; }
+__host__ __device__ inline int attn_rbg(int32_t kvh_rbg, int32_t t0) {
+  return (int)((uint32_t)kvh_rbg >> 16) + ((t0 & kAttnHighItem) << 15);
+}
 constexpr int kAttnMaxItems = 1 << 22;  // split-KV work items of one call (int indices, workspace)
 constexpr int kAcceptRowsMax = 1 << 29; // rows of one acceptance-only call (int offsets)
 constexpr int kAttnWhole = 1;          // flag in AttnItem::t0: the item is its group's only one
+constexpr int kAttnFlags = kAttnWhole | kAttnHighItem;
 constexpr int kAttnWindowPages = 64;   // pages whose block ids a wave holds (one per lane)
 constexpr int kAttnCombineChunks = 8;  // partials the combine loads per round of dependent loads
 

@@ -239,13 +239,13 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
         const int T = group_tokens(i, g, R), pairs = (T + 31) / 32;
         AttnGroup gr{};
         gr.req = i;
-        gr.kvh_rbg = (int32_t)((uint32_t)h | (uint32_t)g << 16);
+        gr.kvh_rbg = attn_pack(h, g);
         gr.first_item = (int32_t)p.items.size();
         auto item = [&](int64_t a, int64_t b) {
           AttnItem it{};
           it.req = i;
           it.kvh_rbg = gr.kvh_rbg;
-          it.t0 = 32 * (int)a | (a == 0 && b == pairs ? kAttnWhole : 0);
+          it.t0 = 32 * (int)a | (a == 0 && b == pairs ? kAttnWhole : 0) | (g >> 16 ? kAttnHighItem : 0);
           it.t1 = std::min(T, 32 * (int)b);
           p.items.push_back(it);
         };
@@ -269,7 +269,10 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
         }
         gr.n_items = (int32_t)p.items.size() - gr.first_item;
         p.max_group_chunks = std::max(p.max_group_chunks, (int)gr.n_items);
-        if (gr.n_items > 1) p.groups.push_back(gr);
+        if (gr.n_items > 1) {
+          if (g >> 16) gr.n_items |= kAttnHighGroup;
+          p.groups.push_back(gr);
+        }
       }
   }
   if (!single) p.first.push_back((int32_t)p.items.size());
@@ -580,7 +583,7 @@ wisp_status run_forward(const Plan &p, const wisp_model *m, const wisp_kv *kv, c
   for (const AttnItem &it : p.items) {
     const int G = p.G;
     const int rows = (int)p.host[p.i_nrow + it.req];
-    const int rbg = (int)((uint32_t)it.kvh_rbg >> 16), tokens = it.t1 - (it.t0 & ~kAttnWhole);
+    const int rbg = attn_rbg(it.kvh_rbg, it.t0), tokens = it.t1 - (it.t0 & ~kAttnFlags);
     const int nr = std::min(p.item_rows, rows * G - rbg * p.item_rows);
     if (rbg == 0) attn_bytes += (double)tokens * kv_tok / p.nkv;
     attn_flops += 4.0 * p.hd * nr * tokens;
@@ -1022,6 +1025,35 @@ wisp_status wisp_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t out[4]) {
     out[1] = c.rb;
     out[2] = c.mt;
     out[3] = c.splits;
+    return WISP_OK;
+  });
+}
+
+wisp_status wisp_attention_plan(const wisp_model *model, const wisp_batch_desc *desc, int32_t out[6],
+                                int32_t *items, int32_t max_items) {
+  return guarded("wisp_attention_plan", [&]() -> wisp_status {
+    wisp_status st;
+    if (!out || max_items < 0 || (max_items > 0 && !items)) return fail(WISP_E_INVALID, "NULL out / items");
+    if ((st = check_model(model, false)) != WISP_OK) return st;
+    if ((st = check_desc(desc, false, true)) != WISP_OK) return st;
+    if (model->dtype != WISP_BF16) return fail(WISP_E_UNSUPPORTED, "the fp32 attention has no plan");
+    Plan p;
+    if (desc->B > 0 && (st = make_plan(p, model, desc, true)) != WISP_OK) return st;
+    out[0] = p.item_rows;
+    out[1] = (int32_t)p.items.size();
+    out[2] = p.attn_waves();
+    out[3] = p.first.empty() ? 0 : 1;
+    out[4] = (int32_t)p.groups.size();
+    out[5] = p.max_group_chunks;
+    const int n = std::min(max_items, out[1]);
+    for (int k = 0, w = 0; k < n; ++k) {
+      const AttnItem &it = p.items[k];
+      if (p.first.empty()) w = k;
+      else while (p.first[w + 1] <= k) ++w;
+      const int32_t v[8] = {it.req, attn_kvh(it.kvh_rbg), attn_rbg(it.kvh_rbg, it.t0), it.t0 & ~kAttnFlags,
+                            it.t1, it.t0 & kAttnWhole, w, 0};
+      std::copy(v, v + 8, items + 8 * (size_t)k);
+    }
     return WISP_OK;
   });
 }
