@@ -139,10 +139,13 @@ int device_cus() {
 }
 
 // Attention work list.  A row group (item_rows of a request's rows x G query rows of one kv
-// head) attends to a run of page pairs; the waves share all groups' pairs in order (request,
-// kv head, row group), and a group that one wave covers alone needs no combine.
+// head) attends to a run of page pairs.  Either every item (a part of a group's pairs) has a
+// wave of its own, or the waves share all groups' pairs in order (request, kv head, row group);
+// a group that one wave covers alone needs no combine.  The times below are of one layer's
+// attention and combine.
 wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<int> &nrow) {
   const int64_t slots = 4 * (int64_t)device_cus();   // one wave per SIMD
+  const bool hd64 = p.hd == 64;
   // a row group's keys end at its last row's causal limit (prompt rows see fewer)
   auto group_tokens = [&](int i, int g, int R) {
     const int last = std::min(nrow[i] * p.G, (g + 1) * R) - 1;
@@ -151,83 +154,148 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
   auto group_pairs = [&](int i, int g, int R) { return (group_tokens(i, g, R) + 31) / 32; };
   auto row_groups = [&](int i, int R) { return (nrow[i] * p.G + R - 1) / R; };
 
+  // The candidates: page pairs of every row group (of one kv head), their time at the rates
+  // measured per pair and launch (ns).  A pair that comes from memory takes about the same
+  // with 32, 48 and 64 rows at head_dim 128, so as few groups per request as fit (128 requests
+  // of up to 36 rows: 246 us with 32 rows, 221 with 48); 64 rows leave head_dim 64 too few
+  // waves (256 requests of 1-8k, one group each: 596 us with 32 rows, 625 with 48, 816 with
+  // 64).  Past 256 rows (prompts: neighbouring groups share the pairs through L2) the products
+  // bound it: 32 rows.
+  constexpr int kRows[3] = {32, 48, 64};
+  constexpr double kStream[2][3] = {{2.8, 2.85, 2.9}, {1.4, 1.45, 1.9}}, kCompute[2][3] = {{1.4, 2.4, 3.3}, {0.7, 1.4, 2.6}};
+  struct Cand {
+    std::vector<int> pairs;
+    int64_t total = 0, most = 0;
+    double us = 0;
+  } cand[3];
   // the largest batch accepted: 2^22 items of at most 48 query rows and 32 page pairs, a round
   // of wave slots kept back (indices are int: what is built below is at most twice as long)
-  int64_t fewest = 0;
-  // Query rows per item, by the time of all pairs at the rates measured per pair and launch
-  // (ns).  A pair that comes from memory: 2.7 with 32 rows (two waves per SIMD), 2.95 and 3.0
-  // with 48 and 64, so as few groups per request as fit; past 256 rows (prompts: neighbouring
-  // groups share the pairs through L2) the products bound it: 1.4, 2.4 and 3.3, so 32 rows.
-  // (4096 prompt rows: 364 us per layer with 32 rows, 436 with 64; 128 requests of up to 68
-  // rows: 623 us with 48, 590 with 64; 32 of up to 36 rows: 38 us with 32, 30 with 48.)
-  constexpr int kRows[3] = {32, 48, 64};
-  constexpr double kStream[3] = {2.7, 2.95, 3.0}, kCompute[3] = {1.4, 2.4, 3.3};
-  double us[3] = {0, 0, 0};
-  for (int i = 0; i < p.B; ++i) {
-    const bool prompt = nrow[i] * p.G > 256;
-    for (int r = 0; r < 3; ++r) {
-      int64_t pairs = 0;
-      for (int g = 0, n = row_groups(i, kRows[r]); g < n; ++g) {
+  int64_t fewest = 0, prompt = 0, unique = 0;   // unique: pairs of the requests' contexts, each once per kv head
+  for (int r = 0; r < 3; ++r) {
+    Cand &c = cand[r];
+    for (int i = 0; i < p.B; ++i) {
+      const bool long_prompt = nrow[i] > WISP_GAMMA_MAX + 1 && nrow[i] * p.G > 256;
+      int64_t n = 0;
+      for (int g = 0, m = row_groups(i, kRows[r]); g < m; ++g) {
         const int pr = group_pairs(i, g, kRows[r]);
-        pairs += pr;
-        if (kRows[r] == 48) fewest += (int64_t)p.nkv * ((pr + 31) / 32);
+        c.pairs.push_back(pr);
+        n += pr;
+        c.most = std::max<int64_t>(c.most, pr);
+        if (r == 1) fewest += (int64_t)p.nkv * ((pr + 31) / 32);
       }
-      us[r] += pairs * (prompt ? kCompute[r] : kStream[r]);
+      c.total += p.nkv * n;
+      c.us += n * (long_prompt ? kCompute : kStream)[hd64][r];
+      if (r == 0) unique += p.nkv * (int64_t)c.pairs.back();
+      if (r == 0 && long_prompt) prompt += p.nkv * n;
     }
   }
   if (fewest > kAttnMaxItems - slots)
     return fail(WISP_E_UNSUPPORTED, "the batch's contexts need %lld attention work items (at most %d)",
                 (long long)fewest, kAttnMaxItems - (int)slots);
-  const int best = us[0] <= us[1] && us[0] <= us[2] ? 0 : us[1] <= us[2] ? 1 : 2;
-  const int R = p.item_rows = kRows[best];
-
-  int64_t total = 0, most = 0, n_groups = 0;   // page pairs of all groups, of the longest; per kv head
-  for (int i = 0; i < p.B; ++i)
-    for (int g = 0, n = row_groups(i, R); g < n; ++g, ++n_groups) {
-      const int64_t pr = group_pairs(i, g, R);
-      total += p.nkv * pr;
-      most = std::max(most, pr);
-    }
+  const Cand *c = nullptr;
   auto count_items = [&](int64_t L) {
     int64_t n = 0;
-    for (int i = 0; i < p.B; ++i)
-      for (int g = 0, m = row_groups(i, R); g < m; ++g) n += p.nkv * ((group_pairs(i, g, R) + L - 1) / L);
-    return n;
+    for (int pr : c->pairs) n += (pr + L - 1) / L;
+    return n * p.nkv;
   };
-  // One item per wave where items of at most 16 pairs (32 with 48 or 64 rows, which have no
-  // second wave per SIMD) fit one wave per SIMD: a group's pairs cut into equal parts of at most
-  // L, the shortest that fits; or, with 32 rows, where items of 16 pairs fit two per SIMD.
-  // (Two on some SIMDs only are slower than one on each: 32 requests of 0.5-2k 30 us per layer
-  // in 1008 items, 38 in 1200; 64 of 0.5-4k 85 us in 2032, 106 in 1032.  48 rows: 22 of 3-4.5k
-  // 63 us in 912 items of 24 pairs, 66 in shares.)  If the groups themselves are more, the
-  // left-over workgroups start as others end.
-  // Beyond that, equal shares of all pairs per wave (64 of 0.5-4k, 14 pairs per wave: 91
-  // instead of 85 us; 4 prompts of 512: 55 instead of 43; 256 of 1-8k, 110 per wave: 610
-  // instead of 692; 48 rows, 64 of 0.5-4k: 90, against 118 in 1040 items).
+  // the shortest items of at least L0 and at most L1 pairs that `waves` waves cover, or 0
+  auto shortest = [&](int64_t L0, int64_t L1, int64_t waves) -> int64_t {
+    if (c->total > L1 * waves || count_items(L1) > waves) return 0;
+    int64_t L = std::max<int64_t>(L0, (c->total + waves - 1) / waves);
+    while (L < L1 && count_items(L) > waves) ++L;
+    return L;
+  };
+
+  // A way to give every item a wave of its own: its items' pairs and its estimated time (us),
+  // the longer of a wave's chain of pairs (starting takes as long as 6, or beside a second wave
+  // 10, 7 at head_dim 64) and of the K and V from memory (pairs that another row group reads too
+  // count 0.3 or, with two waves per SIMD, 0.6), and the combine, 4 us up to 8 items of a group
+  // and 5 + 0.18 per item beyond.  (1 request of 30k, 32 rows: 66 us with items of 12 pairs, 48
+  // with 20, 52 with 32.  4 of 0.5-4k, 8 query heads per kv head: 27 us with 32 rows, 38 with
+  // 48, 46 with 64.  32 of 0.5-2k, 4 heads: 37 us in 944 items of 12 pairs, 46 in 1900 of 6, two
+  // waves per SIMD; at head_dim 64, 16 heads on 16, 35 in 1000 of 24, 32 in 1888 of 10.  12 of
+  // 2-6k, 16 heads on 16: 91 in 1000 of 24, 72 in 1900 of 13.  22 of 3-4.5k and 28-40 rows: 90
+  // in 1984 of 32 rows and 16 pairs, 70 in 1000 of 48 rows and 22.)
+  constexpr double kChain[2][3] = {{1.2, 1.6, 2.0}, {1.0, 1.3, 1.6}};
+  constexpr double kTwo[2] = {2.0, 1.5}, kMem[2][2] = {{3.3, 2.75}, {1.65, 1.4}};   // chain's factor; ns
+  struct Items {
+    int r = 0;
+    int64_t L = 0;   // 0: none
+    double us = 1e30;
+  };
+  // the shortest items of at most L1 pairs that one wave (two) per SIMD cover, or, with one,
+  // longer ones that take less (fewer than two per SIMD would leave loads unissued)
+  auto try_items = [&](Items &best, int r, bool two, int64_t L1) {
+    c = &cand[r];
+    const double pairs = unique + (two ? 0.6 : 0.3) * (c->total - unique);
+    const double mem = pairs * kMem[hd64][two] * 1e-3;
+    for (int64_t l = shortest(2, L1, two ? 2 * slots : slots); l && l <= kAttnWindowPages / 2; ++l) {
+      const int64_t n = (c->most + l - 1) / l;
+      const double chain = two ? (l + (hd64 ? 7 : 10)) * kChain[hd64][r] * kTwo[hd64] : (l + 6) * kChain[hd64][r];
+      const double t = std::max(chain, mem) + (n <= kAttnCombineChunks ? 4.0 : 5.0 + 0.18 * n);
+      if (t < best.us) best = Items{r, l, t};
+      if (two) break;
+    }
+  };
+
   constexpr int64_t kShort = 16;
-  const int64_t one_round = R == 32 ? kShort : 2 * kShort;
-  const bool few = total <= one_round * slots && count_items(one_round) <= slots;
-  const int64_t waves = std::max<int64_t>(1, std::min(R == 32 && !few ? 2 * slots : slots, total));
-  const bool single = few || total <= kShort * waves;
-  int64_t L = std::max<int64_t>(2, (total + waves - 1) / waves);
-  if (single)
-    while (L < (few ? one_round : kShort) && count_items(L) > waves) ++L;
-  if (few) {
-    // Small batches leave wave slots idle even at the shortest items, and their step is
-    // latency-bound: longer items then cost little, while a group of more than
-    // kAttnCombineChunks chunks costs the combine further dependent loads.  Whenever the
-    // items still fit one round of the wave slots, they grow until no group has more
-    // than kAttnCombineChunks of them (B = 1: attention + combine 10.4 + 13.9 -> 14.3 +
-    // 4.2 us per layer; B = 16: 27.7 -> 25.5 us; B = 4 and 8 within 3 %).
-    const int64_t Lc = std::min<int64_t>(kAttnWindowPages / 2, std::max(L, (most + kAttnCombineChunks - 1) / kAttnCombineChunks));
-    if (count_items(Lc) <= slots) L = Lc;
+  const bool prompts = 2 * prompt >= cand[0].total;   // most pairs belong to prompts
+  int best = 0;
+  int64_t L = 0;          // pairs of an item; 0: shares
+  int64_t waves = 0;      // of shares
+  c = &cand[0];
+  if (prompts) {
+    // Up to 16 pairs per wave (two waves per SIMD) the shortest items, one wave each.  Beyond
+    // that items of half a wave's part, dispatched as others end: the items that run at one
+    // time then attend to the same keys, which come from L2, while in shares the waves drift
+    // apart; longer ones save combines, shorter ones even out the end (prompts of 2 x 4000 rows:
+    // 957 us in shares, 829 / 688 / 628 in items of 16 / 32 / 64 pairs; 2048 rows: 150 us in
+    // shares, 115 in items of 24, 95 of 128).
+    L = shortest(2, kShort, slots);
+    if (!L) {
+      L = std::max<int64_t>(2, (c->total + 2 * slots - 1) / (2 * slots));
+      if (L > kShort) L = std::min<int64_t>(256, std::max<int64_t>(24, L / 2));
+      else
+        while (L < kShort && count_items(L) > 2 * slots) ++L;
+    }
+  } else {
+    // Items of up to 32 pairs where one wave per SIMD covers them, or of up to 16 (24 with 48 rows)
+    // where two do and have room; equal shares of all pairs per wave where that is estimated to
+    // take less (its pairs at the rate of kStream and 20 us, 12 at head_dim 64), and beyond.
+    // (256 of 1-8k, 110 pairs per wave: 610 us in shares, 692 in items; 48 rows, 64 of 0.5-4k:
+    // 90, against 118 in 1040 items; 22 of 3-4.5k 66, against 63 in 912 items of 24 pairs.)
+    // Where the row groups alone outnumber the waves, items of up to 16 pairs, dispatched as
+    // others end.
+    for (int r = 1; r < 3; ++r)
+      if (cand[r].us < cand[best].us) best = r;
+    const bool two = kRows[best] == 32 || (hd64 && kRows[best] == 48);   // waves per SIMD of shares
+    waves = two ? 2 * slots : slots;
+    Items a;
+    if (cand[best].total > kShort * waves) a.us = p.nkv * cand[best].us * 1e-3 + (hd64 ? 12.0 : 20.0);
+    for (int r = 0; r < 3; ++r) try_items(a, r, false, 2 * kShort);
+    try_items(a, 0, true, kShort);
+    if (hd64) try_items(a, 1, true, 24);
+    if (a.L) best = a.r;
+    c = &cand[best];
+    L = a.L;
+    if (!L && c->total <= kShort * waves) L = kShort;
+    // At head_dim 64, where row groups share their pairs, items of 24 pairs (more where that
+    // would make more than 16 per SIMD) in turn rather than shares, which run the groups that
+    // share one after another (256 of 1-8k, 8 query heads per kv head: 419 us in shares, 399 in
+    // items; 64 of 1-3k, 128-136 rows: 153 and 131)
+    if (!L && hd64 && 5 * c->total > 6 * unique)
+      L = std::min<int64_t>(256, std::max<int64_t>(24, c->total / (16 * slots)));
   }
+  const int R = p.item_rows = kRows[best];
+  const int64_t total = c->total;
+  const bool single = L > 0;
+  if (!single) waves = std::min(waves, total);
   // shares: wave w starts at pair w * total / waves, moved to a group's edge if one is within
   // 1/16 of a share (a sliver of a group costs an item and a partial, 1/16 more a little time)
-  const int64_t snap = total / waves / 16;
+  const int64_t snap = single ? 0 : total / waves / 16;
   int64_t at = 0, w = 0;       // pairs before this group; wave of the last item
   auto start = [&](int64_t k) { return k * total / waves; };
-  p.items.reserve(single ? count_items(L) : waves + (int64_t)p.nkv * n_groups);
+  p.items.reserve(single ? count_items(L) : waves + (int64_t)p.nkv * (int64_t)c->pairs.size());
   if (!single) {
     p.first.reserve(waves + 1);
     p.first.push_back(0);

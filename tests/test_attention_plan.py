@@ -71,3 +71,25 @@ def test_one_request_of_more_than_65536_row_groups():
     p = check(64, 1, 64, [0], [W.GAMMA_MAX], [W.PREFILL_MAX])
     assert p["items"][:, 2].max() == -(-(W.PREFILL_MAX + W.GAMMA_MAX + 1) * 64 // p["rows"]) - 1
     check(128, 2, 64, [5, 3], [W.GAMMA_MAX, 2], [W.PREFILL_MAX, 40])
+
+
+@pytest.mark.parametrize("n_q,n_kv,hd,ctx,gamma,prefill,rows,shares", [
+    # latency: a few requests take 32-row items whatever their heads, and one wave per item
+    (64, 8, 128, [500, 900, 2000, 4000], [2, 8, 5, 1], None, 32, False),
+    (32, 2, 128, [1200], [8], None, 32, False),
+    (64, 8, 64, [2000, 8000], [8, 8], None, 32, False),
+    # long contexts of few requests: more items per group than one round of the combine
+    (32, 8, 128, [30000], [8], None, 32, False),
+    # prompts: 32-row items, dispatched in turn
+    (64, 8, 128, [0, 0], [2, 2], [4000, 4000], 32, False),
+    (32, 8, 128, [500, 0], [5, 5], [0, 2048], 32, False),
+    # many requests: shares of 48 or 64 rows; at head_dim 64 items where row groups share keys
+    (32, 8, 128, [1000 + 27 * k for k in range(256)], [k % 9 for k in range(256)], None, 48, True),
+    (64, 8, 128, [1000 + 27 * k for k in range(256)], [k % 8 for k in range(256)], None, 64, True),
+    (64, 8, 64, [1000 + 27 * k for k in range(256)], [k % 8 for k in range(256)], None, 48, False),
+])
+def test_choices(n_q, n_kv, hd, ctx, gamma, prefill, rows, shares):
+    p = check(n_q, n_kv, hd, ctx, gamma, prefill)
+    assert (p["rows"], p["shares"]) == (rows, shares), (p["rows"], p["shares"], p["waves"])
+    if len(ctx) == 1 and ctx[0] == 30000:
+        assert p["most"] > 8 and p["waves"] <= 1024
