@@ -212,9 +212,11 @@ wisp_status wisp_verify(const wisp_model *model, const wisp_kv *kv, const wisp_b
  *           id outside [0, vocab), 2: a block id outside [0, n_blocks)); the caller zeroes it
  *           and reads it after synchronising.  With NULL, faults go unreported.
  * A batch whose scratch (wisp_workspace_size, plus wisp_logits_workspace_size when
- * target_logits is NULL) exceeds WISP_NOALLOC_SCRATCH_BYTES returns WISP_E_WORKSPACE before
- * any GPU work.  Every call on one GPU shares that GPU's array: calls that overlap on it
- * (other streams, other threads) race and must be serialised by the caller.
+ * target_logits is NULL) exceeds WISP_NOALLOC_SCRATCH_BYTES runs with fewer partial results of
+ * the attention if it then fits (contexts in fewer parts: results within rounding of
+ * wisp_verify's), and returns WISP_E_WORKSPACE before any GPU work otherwise.  Every call on one
+ * GPU shares that GPU's array: calls that overlap on it (other streams, other threads) race
+ * and must be serialised by the caller.
  */
 #define WISP_NOALLOC_SCRATCH_BYTES (128u << 20)
 wisp_status wisp_verify_noalloc(const wisp_model *model, const wisp_kv *kv, const wisp_batch_desc *desc,

@@ -131,7 +131,7 @@ void attention_f32(const StepDesc &d, int M, const float *q, const float *k_pool
                    hipStream_t s);
 
 // ----- acceptance ----------------------------------------------------------------------------
-struct SamplerScratch {   // carved from the workspace; CH = sampler_chunks(V), RC = sampler_race_chunks(V)
+struct SamplerScratch {   // carved from the workspace; CH = sampler_chunks(V), RC race chunks
   float *part_m;          // [M][CH] chunk maxima
   int32_t *part_i;        // [M][CH] chunk argmax (greedy)
   double *part_s;         // [M][CH] chunk sums of exp(z - the chunk's maximum)
@@ -140,9 +140,10 @@ struct SamplerScratch {   // carved from the workspace; CH = sampler_chunks(V), 
   int32_t *req_R;         // [B] first rejection
 };
 int sampler_chunks(int V);
-int sampler_race_chunks(int V);
+// entries per race chunk of a batch, at most `bytes` of race winners (if 8192 are enough for that)
+int sampler_race_chunk(int B, int V, size_t bytes);
 void sampler(const StepDesc &d, int B, int M, int V, const float *logits, const int32_t *tokens,
-             const float *q, float T, uint64_t seed, SamplerScratch sc, int32_t *accept_len,
+             const float *q, float T, uint64_t seed, int chunk, SamplerScratch sc, int32_t *accept_len,
              int32_t *out_tokens, hipStream_t s);
 void uniform_draws(uint64_t seed, uint32_t req, uint32_t tag, uint32_t row, uint32_t n, float *out,
                    hipStream_t s);

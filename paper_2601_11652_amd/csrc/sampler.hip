@@ -29,7 +29,8 @@ __device__ __forceinline__ Philox4 draw(uint64_t seed, uint32_t c0, uint32_t row
 // ---------------------------------------------------------------------------------------
 constexpr int kVChunk = 8192;
 // The race takes chunks of 2048 entries (8 per thread), doubled up to 8192 while they make more
-// than kRaceGroups workgroups: a workgroup also decides the request's drafts, which costs
+// than kRaceGroups workgroups (or, in a step, than fit into the GEMMs' partial sums, which are
+// free by then): a workgroup also decides the request's drafts, which costs
 // about as much as 2048 entries, but fewer than that many workgroups leave SIMDs idle (with
 // 4-byte loads: B = 32 27.4 us with chunks of 8192, 18.3 with 2048; B = 256 119 against 143).
 constexpr int kRaceChunk = 2048, kRaceChunkMax = 8192, kRaceGroups = 2560;
@@ -378,16 +379,19 @@ __global__ __launch_bounds__(64) void finalize_kernel(StepDesc d, const int32_t 
 }
 
 int sampler_chunks(int V) { return (V + kVChunk - 1) / kVChunk; }
-int sampler_race_chunks(int V) { return (V + kRaceChunk - 1) / kRaceChunk; }
+int sampler_race_chunk(int B, int V, size_t bytes) {
+  auto chunks = [&](int chunk) { return (V + chunk - 1) / chunk; };
+  int chunk = kRaceChunk;
+  while (chunk < kRaceChunkMax && ((int64_t)B * chunks(chunk) > kRaceGroups || (size_t)B * chunks(chunk) * 16 > bytes)) chunk *= 2;
+  return chunk;
+}
 
 void sampler(const StepDesc &d, int B, int M, int V, const float *logits, const int32_t *tokens,
-             const float *q, float T, uint64_t seed, SamplerScratch sc, int32_t *accept_len,
+             const float *q, float T, uint64_t seed, int chunk, SamplerScratch sc, int32_t *accept_len,
              int32_t *out_tokens, hipStream_t s) {
   if (B == 0) return;
   const int CH = sampler_chunks(V);
-  int chunk = kRaceChunk;
-  while (chunk < kRaceChunkMax && (int64_t)B * ((V + chunk - 1) / chunk) > kRaceGroups) chunk *= 2;
-  const int RC = (V + chunk - 1) / chunk;   // at most sampler_race_chunks(V)
+  const int RC = (V + chunk - 1) / chunk;
   const bool vec = V % 4 == 0 && ((uintptr_t)logits & 15) == 0;
   launch(vec ? row_stats_kernel<true> : row_stats_kernel<false>, dim3(M, CH), 256, 0, s, logits, V, T, CH, sc.part_m,
          sc.part_i, sc.part_s);

@@ -60,6 +60,7 @@ struct Plan {
          w_part = 0, w_attn_o = 0, w_attn_ml = 0, w_sm = 0, w_si = 0, w_ss = 0, w_rk = 0, w_ri = 0,
          w_rR = 0, w_vtok = 0, total = 0;
   int max_group_chunks = 0;          // most chunks any attention group combines
+  int race_chunk = 0;                // vocabulary entries per workgroup of the acceptance's race
 };
 
 
@@ -129,6 +130,26 @@ void carve(size_t &w, size_t &field, size_t bytes) {
   w = align256(w + bytes);
 }
 
+// the logits of a step's verification rows
+size_t logits_bytes(int64_t rows, int V) { return align256((size_t)rows * (size_t)V * sizeof(float)); }
+
+// the race winners of every (request, chunk): keys, then token ids
+size_t race_bytes(const Plan &p) {
+  const size_t RC = (std::max(p.V, 1) + p.race_chunk - 1) / p.race_chunk;
+  return 2 * align256((size_t)p.B * RC * 2 * 4);
+}
+void place_race(Plan &p, size_t at) {
+  p.w_rk = at;
+  p.w_ri = at + race_bytes(p) / 2;
+}
+
+// partial results of one attention item: O and (m, l) of its rows
+size_t attn_item_bytes(const Plan &p) { return (size_t)p.item_rows * (p.hd + 2) * 4; }
+// the space of all of them (none where every group is one item)
+size_t attn_part_bytes(const Plan &p) {
+  return p.max_group_chunks > 1 ? align256(p.items.size() * (size_t)p.hd * p.item_rows * 4) + align256(p.items.size() * (size_t)p.item_rows * 2 * 4) : 0;
+}
+
 // compute units of the current device (the attention work list is sized to them)
 int device_cus() {
   int dev = 0, n = 0;
@@ -141,9 +162,13 @@ int device_cus() {
 // Attention work list.  A row group (item_rows of a request's rows x G query rows of one kv
 // head) attends to a run of page pairs.  Either every item (a part of a group's pairs) has a
 // wave of its own, or the waves share all groups' pairs in order (request, kv head, row group);
-// a group that one wave covers alone needs no combine.  The times below are of one layer's
-// attention and combine.
-wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<int> &nrow) {
+// a group that one wave covers alone needs no combine.  The partial results take at most `room`
+// bytes.  The times below are of one layer's attention and combine.
+wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<int> &nrow, size_t room) {
+  p.items.clear();
+  p.groups.clear();
+  p.first.clear();
+  p.max_group_chunks = 0;
   const int64_t slots = 4 * (int64_t)device_cus();   // one wave per SIMD
   const bool hd64 = p.hd == 64;
   // a row group's keys end at its last row's causal limit (prompt rows see fewer)
@@ -288,6 +313,13 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
   }
   const int R = p.item_rows = kRows[best];
   const int64_t total = c->total;
+  // longer items where the partials would pass the room, at the longest one item per group
+  // and no partials
+  const int64_t cap = (int64_t)(std::min<size_t>(room, INT64_MAX) / attn_item_bytes(p));
+  if ((L ? count_items(L) : waves + p.nkv * (int64_t)c->pairs.size()) > cap) {
+    if (!L) L = std::max<int64_t>(2, (total + waves - 1) / waves);
+    while (L < c->most && count_items(L) > cap) L = std::min(c->most, L + std::max<int64_t>(1, L / 8));
+  }
   const bool single = L > 0;
   if (!single) waves = std::min(waves, total);
   // shares: wave w starts at pair w * total / waves, moved to a group's edge if one is within
@@ -347,8 +379,13 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
   return WISP_OK;
 }
 
-// forward=true: the full step; false: acceptance only (rows/drafts of the batch, vocab V)
-wisp_status make_plan(Plan &p, const wisp_model *m, const wisp_batch_desc *d, bool forward, int vocab = 0) {
+void lay_out(Plan &p, const wisp_batch_desc *d, bool forward, const std::vector<int> &off, const std::vector<int> &doff,
+             const std::vector<int> &voff, const std::vector<int> &nrow);
+
+// forward=true: the full step; false: acceptance only (rows/drafts of the batch, vocab V).
+// limit: the most bytes the workspace should take, kept by fewer attention partials if that helps.
+wisp_status make_plan(Plan &p, const wisp_model *m, const wisp_batch_desc *d, bool forward, int vocab = 0,
+                      size_t limit = SIZE_MAX) {
   p.B = d->B;
   p.V = forward ? m->vocab : vocab;
   // rows of request i: prefill_len prompt rows (forward only), root, gamma drafts; the
@@ -387,10 +424,24 @@ wisp_status make_plan(Plan &p, const wisp_model *m, const wisp_batch_desc *d, bo
       p.g_lm = gemm_bf16_plan(p.Mv, p.V, p.d);
       p.g_lm.splits = 1;
       p.g_lm.kf_per_split = p.d / 16;
-      wisp_status st = plan_attention(p, d, nrow);
+      wisp_status st = plan_attention(p, d, nrow, SIZE_MAX);
       if (st != WISP_OK) return st;
     }
   }
+  lay_out(p, d, forward, off, doff, voff, nrow);
+  for (int k = 0; k < 4 && forward && p.total > limit; ++k) {
+    const size_t rest = p.total - attn_part_bytes(p);
+    if (attn_part_bytes(p) == 0 || rest > limit) break;
+    const wisp_status st = plan_attention(p, d, nrow, k < 3 ? limit - rest : 0);
+    if (st != WISP_OK) return st;
+    lay_out(p, d, forward, off, doff, voff, nrow);
+  }
+  return WISP_OK;
+}
+
+// the descriptor block and the workspace of a plan
+void lay_out(Plan &p, const wisp_batch_desc *d, bool forward, const std::vector<int> &off, const std::vector<int> &doff,
+             const std::vector<int> &voff, const std::vector<int> &nrow) {
   // descriptor block
   size_t n = 0;
   auto take = [&](size_t &f, size_t cnt) {
@@ -440,9 +491,6 @@ wisp_status make_plan(Plan &p, const wisp_model *m, const wisp_batch_desc *d, bo
   carve(w, p.w_si, (size_t)p.Mv * CH * 4);
   carve(w, p.w_ss, (size_t)p.Mv * CH * 8);
   carve(w, p.w_vtok, (size_t)(p.prefill ? p.Mv : 0) * 4);
-  const int RC = sampler_race_chunks(std::max(p.V, 1));
-  carve(w, p.w_rk, (size_t)p.B * RC * 2 * 4);
-  carve(w, p.w_ri, (size_t)p.B * RC * 2 * 4);
   carve(w, p.w_rR, (size_t)p.B * 4);
   if (forward) {
     const size_t es = p.bf16 ? 2 : 4;
@@ -459,12 +507,21 @@ wisp_status make_plan(Plan &p, const wisp_model *m, const wisp_batch_desc *d, bo
     } else {
       part = std::max({(size_t)p.qkvN, (size_t)p.d, (size_t)2 * p.F});
     }
-    carve(w, p.w_part, part * p.M * 4);
-    carve(w, p.w_attn_o, p.items.size() * (size_t)p.hd * p.item_rows * 4);
-    carve(w, p.w_attn_ml, p.items.size() * (size_t)p.item_rows * 2 * 4);
+    part *= (size_t)p.M * 4;
+    p.race_chunk = sampler_race_chunk(p.B, p.V, part);
+    carve(w, p.w_part, std::max(part, race_bytes(p)));
+    place_race(p, p.w_part);   // the partial sums are free when the acceptance starts
+    if (p.max_group_chunks > 1) {
+      carve(w, p.w_attn_o, p.items.size() * (size_t)p.hd * p.item_rows * 4);
+      carve(w, p.w_attn_ml, p.items.size() * (size_t)p.item_rows * 2 * 4);
+    }
+  } else {
+    p.race_chunk = sampler_race_chunk(p.B, std::max(p.V, 1), SIZE_MAX);
+    size_t at = 0;
+    carve(w, at, race_bytes(p));
+    place_race(p, at);
   }
   p.total = w;
-  return WISP_OK;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -752,9 +809,10 @@ wisp_status check_verify(const wisp_model *model, const wisp_kv *kv, const wisp_
   return WISP_OK;
 }
 
-wisp_status plan_verify(Plan &p, const wisp_model *model, const wisp_batch_desc *desc, const float *draft_probs) {
+wisp_status plan_verify(Plan &p, const wisp_model *model, const wisp_batch_desc *desc, const float *draft_probs,
+                        size_t limit = SIZE_MAX) {
   wisp_status st;
-  if ((st = make_plan(p, model, desc, true)) != WISP_OK) return st;
+  if ((st = make_plan(p, model, desc, true, 0, limit)) != WISP_OK) return st;
   if (p.S > 0 && !draft_probs) return fail(WISP_E_INVALID, "draft_probs is NULL");
   if (!p.bf16 && p.max_tokens > 32768) return fail(WISP_E_UNSUPPORTED, "fp32 path supports <= 32768 tokens per request");
   return WISP_OK;
@@ -784,7 +842,7 @@ wisp_status run_verify(const Plan &p, const wisp_model *model, const wisp_kv *kv
   }
   // algorithmic bytes: one fp32 pass over the logits plus one logits row and one q row per request
   ProfScope ps(WISP_PROF_SAMPLER, (double)p.Mv * p.V * 4.0 + 2.0 * p.B * p.V * 4.0, 0, s);
-  sampler(sv, p.B, p.Mv, p.V, target_logits, vtok, draft_probs, desc->temperature, rng_seed,
+  sampler(sv, p.B, p.Mv, p.V, target_logits, vtok, draft_probs, desc->temperature, rng_seed, p.race_chunk,
           sampler_scratch(p, ws), accept_len, out_tokens, s);
   return hip_check("sampler launch");
 }
@@ -876,7 +934,7 @@ size_t wisp_logits_workspace_size(const wisp_model *model, const wisp_batch_desc
     if (check_model(model, false) != WISP_OK || check_desc(desc, false, true) != WISP_OK) return 0;
     Plan p;
     if (make_plan(p, model, desc, true) != WISP_OK) return 0;
-    return align256((size_t)p.Mv * (size_t)p.V * sizeof(float));
+    return logits_bytes(p.Mv, p.V);
   });
 }
 
@@ -942,7 +1000,7 @@ wisp_status wisp_verify(const wisp_model *model, const wisp_kv *kv, const wisp_b
     Plan p;
     if ((st = plan_verify(p, model, desc, draft_probs)) != WISP_OK) return st;
     // without a caller buffer the logits live in the workspace, after everything else
-    const size_t need = p.total + (target_logits ? 0 : align256((size_t)p.Mv * (size_t)p.V * sizeof(float)));
+    const size_t need = p.total + (target_logits ? 0 : logits_bytes(p.Mv, p.V));
     if (workspace_bytes < need)
       return fail(WISP_E_WORKSPACE, "workspace %zu bytes < %zu needed", workspace_bytes, need);
     hipStream_t s = (hipStream_t)stream;
@@ -963,8 +1021,12 @@ wisp_status wisp_verify_noalloc(const wisp_model *model, const wisp_kv *kv, cons
     if ((st = check_verify(model, kv, desc, tokens, accept_len, out_tokens)) != WISP_OK) return st;
     if (desc->B == 0) return WISP_OK;
     Plan p;
-    if ((st = plan_verify(p, model, desc, draft_probs)) != WISP_OK) return st;
-    const size_t need = p.total + (target_logits ? 0 : align256((size_t)p.Mv * (size_t)p.V * sizeof(float)));
+    // attention partials beyond the scratch would refuse the batch: fewer of them then
+    int64_t rows = 0;
+    for (int i = 0; i < desc->B; ++i) rows += desc->gamma[i] + 1;
+    const size_t scratch_bytes = WISP_NOALLOC_SCRATCH_BYTES, logits = target_logits ? 0 : logits_bytes(rows, model->vocab);
+    if ((st = plan_verify(p, model, desc, draft_probs, logits < scratch_bytes ? scratch_bytes - logits : 0)) != WISP_OK) return st;
+    const size_t need = p.total + logits;
     if (need > (size_t)WISP_NOALLOC_SCRATCH_BYTES)
       return fail(WISP_E_WORKSPACE, "the batch needs %zu bytes of scratch, more than the %zu of the static "
                   "per-device scratch (use wisp_verify with a workspace)", need, (size_t)WISP_NOALLOC_SCRATCH_BYTES);
@@ -998,7 +1060,7 @@ wisp_status wisp_accept(const wisp_batch_desc *desc, int32_t vocab, const float 
     char *ws = (char *)workspace;
     if ((st = upload(p, ws, s)) != WISP_OK) return st;
     StepDesc sd = step_desc(p, ws, desc, 0);
-    sampler(sd, p.B, p.M, vocab, logits, tokens, draft_probs, desc->temperature, rng_seed,
+    sampler(sd, p.B, p.M, vocab, logits, tokens, draft_probs, desc->temperature, rng_seed, p.race_chunk,
             sampler_scratch(p, ws), accept_len, out_tokens, s);
     return hip_check("sampler launch");
   });

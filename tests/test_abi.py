@@ -261,3 +261,30 @@ def test_noalloc_rejects_batches_beyond_its_static_scratch(W):
     assert st == W.WISP_E_WORKSPACE, st
     assert "static" in W.wisp_last_error()
     assert W.wisp_workspace_size(m, big) > 128 << 20
+
+
+def _noalloc(W, shape, B, gamma, ctx, logits):
+    d, nq, nkv, hd, F, V, dtype = shape
+    m = _model(W, d_model=d, n_q_heads=nq, n_kv_heads=nkv, head_dim=hd, d_ff=F, vocab=V, dtype=dtype)
+    desc = _desc(W, [ctx] * B, [gamma] * B, stride=ctx // 16 + 2)
+    kv = W.wisp_kv(FAKE, FAKE, 100000, 16)
+    return W.load_library().wisp_verify_noalloc(C.byref(m), C.byref(kv), C.byref(desc.c), FAKE, FAKE, 1, FAKE, FAKE,
+                                                FAKE if logits else None, None, None)
+
+
+_8B, _70B = (4096, 32, 8, 128, 14336, 128256, 1), (8192, 64, 8, 128, 28672, 128256, 1)
+
+
+@pytest.mark.parametrize("shape,B,gamma,ctx,logits", [
+    (_8B, 82, 5, 1000, True), (_8B, 83, 5, 1000, True), (_8B, 85, 5, 1000, True), (_8B, 130, 3, 1000, True), (_8B, 196, 1, 1000, True),
+    (_70B, 74, 3, 1000, True), (_8B, 78, 1, 1000, False), (_8B, 134, 0, 1000, False), (_70B, 9, 12, 2761, False),
+    ((2048, 16, 16, 128, 5504, 32000, 1), 25, 14, 1986, False), ((1024, 16, 2, 64, 2048, 32000, 1), 137, 16, 3297, True),
+    ((64, 2, 2, 32, 64, 836448, 0), 40, 0, 100, False)])
+def test_noalloc_takes_batches_at_its_scratch_limit(W, shape, B, gamma, ctx, logits):
+    """Batches whose workspace lies at the static scratch's size: attention partials and race
+    chunks that would pass it are fewer there, so none of these is refused.  Without a GPU the
+    call ends after planning (WISP_E_HIP); the fake pointers are never used."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("would run on the GPU, with pointers that are not there")
+    assert _noalloc(W, shape, B, gamma, ctx, logits) == W.WISP_E_HIP, W.wisp_last_error()

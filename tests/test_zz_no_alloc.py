@@ -3,7 +3,8 @@ wisp_verify through the C ABI: two calls in a row on one GPU, the second with a 
 batch, on the fp32 and the bf16 model.  Same kernels and plan, so the outputs (logits,
 accept lengths, emitted tokens) and the KV written into the pools must be identical to
 the workspace path's, bit for bit; a token id out of range is reported through the
-caller's fault word and not through later clean calls."""
+caller's fault word and not through later clean calls.  A batch whose attention partials alone
+would pass the static scratch runs with fewer of them: the same results within rounding."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +12,7 @@ import torch
 import paper_2601_11652_amd as W
 import wisp_inputs as wi
 from oracle import fixtures as fx
-from gpu_harness import Workload, gpu_model, log, pools_to_dev, to_dev
+from gpu_harness import Workload, check_decisions_on_gpu_logits, gpu_model, log, pools_to_dev, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +83,50 @@ def test_noalloc_reports_faults_in_the_callers_word():
     W.wisp_verify_noalloc(gm.c, kv, desc, good, q, 3, acc, out, logits, fault)
     torch.cuda.synchronize()
     assert int(fault.item()) == 0
+
+
+@pytest.mark.parametrize("n_kv,hd,ctx", [(4, 128, 500), (8, 64, 2000)], ids=["whole groups", "longer items"])
+def test_noalloc_with_fewer_attention_partials(n_kv, hd, ctx):
+    """120 requests of 17 rows: the workspace of wisp_verify passes the static scratch, through
+    its partials; noalloc cuts the contexts into fewer parts (or none).  Logits within the
+    stated bf16 bound of wisp_verify's, 2e-2 max-abs, K/V within two bf16 roundings of values of
+    that size, decisions as the oracle takes them on the same logits."""
+    shape = wi.ModelShape(f"noalloc-{n_kv}", 1, 512, 32, n_kv, hd, 512, 1024, "bf16", 10000.0)
+    B, gamma = 120, 16
+    mix = wi.custom_mix(shape, [ctx + 3 * k for k in range(B)], [gamma] * B, name="noalloc-big")
+    pt, nb = wi.page_table(mix)
+    gm = gpu_model(shape)
+    desc = W.BatchDesc(mix.ctx_len, mix.gamma, to_dev(pt), 1.0, mix.req_id)
+    need = W.wisp_workspace_size(gm.c, desc)
+    log(f"{shape.name}: workspace {need >> 20} MiB")
+    assert need > 128 << 20
+    g = torch.Generator(device="cuda")
+    g.manual_seed(17)
+    pool = lambda: torch.randn(1, nb, n_kv, 16 * hd, device="cuda", generator=g).to(torch.bfloat16)
+    k0, v0 = pool(), pool()
+    q = torch.softmax(2.5 * torch.randn(B * gamma, shape.vocab, device="cuda", generator=g), -1)
+    tokens = torch.randint(0, shape.vocab, (mix.M,), device="cuda", dtype=torch.int32, generator=g)
+    res = []
+    for noalloc in (False, True, True):
+        kv = W.KVPool(k0.clone(), v0.clone())
+        acc = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+        out = torch.full((mix.M,), -7, dtype=torch.int32, device="cuda")
+        logits = torch.full((mix.M, shape.vocab), float("nan"), device="cuda")
+        if noalloc:
+            fault = torch.zeros(1, dtype=torch.int32, device="cuda")
+            W.wisp_verify_noalloc(gm.c, kv, desc, tokens, q, 5, acc, out, logits, fault)
+            assert int(fault.item()) == 0
+        else:
+            ws = W.workspace(need)
+            W.wisp_verify(gm.c, kv, desc, tokens, q, 5, acc, out, logits, ws)
+            W.wisp_check(ws)
+        res.append((logits, kv.k, kv.v, acc, out))
+    d = (res[1][0] - res[0][0]).abs().max().item()
+    log(f"  logits differ by at most {d:.3e}")
+    assert d <= 2e-2
+    for a, b in zip(res[0][1:3], res[1][1:3]):
+        assert ((a.float() - b.float()).abs() <= 2 * 2.0 ** -8 * a.float().abs().max()).all()
+    for a, b in zip(res[1], res[2]):
+        assert torch.equal(a, b)
+    n = [x.cpu().numpy() for x in (res[1][3], res[1][4], res[1][0], tokens, q)]
+    check_decisions_on_gpu_logits(n[0], n[1], n[2], n[3], n[4], mix.gamma, 1.0, 5, req_id=mix.req_id)
