@@ -93,3 +93,11 @@ def test_choices(n_q, n_kv, hd, ctx, gamma, prefill, rows, shares):
     assert (p["rows"], p["shares"]) == (rows, shares), (p["rows"], p["shares"], p["waves"])
     if len(ctx) == 1 and ctx[0] == 30000:
         assert p["most"] > 8 and p["waves"] <= 1024
+
+
+def test_gpu_cases_take_the_plan_they_are_written_for():
+    """The cases of the attention's GPU tests name rows per group and shares."""
+    import test_gpu_attention_shares as t
+    for name, ctx, gamma, prefill, n_q, n_kv, hd, plan in t.CASES:
+        assert t._plan(ctx, gamma, prefill, n_q, n_kv, hd) == plan, name
+    assert {(p, c[6]) for *c, p in t.CASES} >= {((r, True), h) for r in (32, 48, 64) for h in (64, 128)}
