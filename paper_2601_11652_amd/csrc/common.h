@@ -36,11 +36,9 @@ __device__ __forceinline__ uint32_t pack2bf_rne(float a, float b) {
 
 template <typename T> struct Act;
 template <> struct Act<float> {
-  static __device__ __forceinline__ float load(const float *p, int64_t i) { return p[i]; }
   static __device__ __forceinline__ void store(float *p, int64_t i, float v) { p[i] = v; }
 };
 template <> struct Act<uint16_t> {
-  static __device__ __forceinline__ float load(const uint16_t *p, int64_t i) { return bf2f(p[i]); }
   static __device__ __forceinline__ void store(uint16_t *p, int64_t i, float v) { p[i] = f2bf(v); }
 };
 

@@ -147,6 +147,5 @@ void sampler(const StepDesc &d, int B, int M, int V, const float *logits, const 
              int32_t *out_tokens, hipStream_t s);
 void uniform_draws(uint64_t seed, uint32_t req, uint32_t tag, uint32_t row, uint32_t n, float *out,
                    hipStream_t s);
-void clear_ints(int *p, int n, hipStream_t s);
 
 }  // namespace wisp

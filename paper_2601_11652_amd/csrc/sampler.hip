@@ -415,10 +415,4 @@ void uniform_draws(uint64_t seed, uint32_t req, uint32_t tag, uint32_t row, uint
   launch(uniform_kernel, blocks, 256, 0, s, seed, req, tag, row, n, out);
 }
 
-__global__ void clear_ints_kernel(int *p, int n) {
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) p[k] = 0;
-}
-
-void clear_ints(int *p, int n, hipStream_t s) { launch(clear_ints_kernel, 1, 64, 0, s, p, n); }
-
 }  // namespace wisp
