@@ -4,8 +4,8 @@
 // request's block table.
 //
 // bf16 path, a work item being (request, kv head, group of 32, 48 or 64 query rows, token
-// range) and a wave running one or several of them.  Per 32 tokens (a page pair) the wave computes S^T = K Q^T and O^T += V^T P^T
-// with v_mfma_f32_16x16x32_bf16.  Computing the transposed products keeps every query row
+// range) and a wave running one or several of them.  Per 32 tokens (a page pair) the wave
+// computes S^T = K Q^T and O^T += V^T P^T with v_mfma_f32_16x16x32_bf16.  Computing the transposed products keeps every query row
 // in one lane column (lane % 16), so the online softmax needs only two cross-row steps
 // (VALU lane swaps),
 // and the probabilities leave the first product in exactly the register order the second
@@ -23,14 +23,15 @@ namespace wisp {
 
 // Bound by HBM for decode batches and by its own serial chain (products, softmax, products)
 // for prompts.  Wave w of the launch runs items first[w] .. first[w + 1] - 1 one after
-// another (item w alone without that list), 4 waves per workgroup, two per SIMD with 32 query rows and one otherwise.  The
-// loads run one page pair ahead of the products, across items, so 16 KiB per wave stay in
+// another (item w alone without that list), 4 waves per workgroup.  A SIMD holds two waves of 32
+// query rows and one of 48 or 64; at head_dim 64 four, two and one.  The loads run one page pair ahead of the products, across items, so 16 KiB per wave stay in
 // flight and what an item costs besides its pairs (descriptor, block ids, query rows) loads
 // while the one before is computed; a context that one wave covers alone is written without
 // a combine.  Measured per layer, against one wave per item of at most 32 pairs with the query
 // rows in registers: 256 requests of 1-8k tokens 692 -> 610 us (6.0 TB/s; random 4 KiB pages
-// alone stream at 6.6), 128 requests of 0.25-32k 661 -> 590 us, a prompt of 4096 rows
-// 415 -> 364 us; 32 requests of 0.5-2k (one item per wave either way) 30 us in both.
+// alone stream at 6.6), 128 requests of 0.25-32k 661 -> 590 us; 32 requests of
+// 0.5-2k (one item per wave either way) 30 us in both; a prompt of 4096 rows with its combine
+// 511 -> 364 us.
 template <int HD, int RB>
 __global__ __launch_bounds__(256, RB == 2 ? 2 : 1) void attn_bf16_kernel(StepDesc d, const AttnItem *__restrict__ items,
                                                            const int32_t *__restrict__ first, int n_waves,

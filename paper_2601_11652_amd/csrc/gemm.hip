@@ -226,7 +226,7 @@ static constexpr int kRingMaxMT1 = 2, kRingMaxMT2 = 5;
 //     alone fill a round of the 256 CUs (>= kWideTiles: the 70B gate/up, the LM heads), since
 //     they read the activations half as often: 70B gate/up at 128 rows 198 -> 146 us, at 171
 //     rows 243 -> 184 us (128 columns: 210), the 8B LM head at 171 rows 257 -> 230 us;
-//   9-12: one row block of 384 rows as two 192 x 256 tiles side by side (70B at 370 rows:
+//   9-12: two 192 x 256 tiles side by side, weights from L2 for the second (70B at 370 rows:
 //     gate/up 384 -> 320 us against a 384 x 128 tile, 347 us in this kernel);
 //   beyond (> 384 rows): 256 x 256 tiles, or 192 x 256 where kTileUs estimates at least an
 //     eighth less time: fewer padded rows or fuller rounds (8B at 1291 rows: QKV 87 -> 74,

@@ -324,17 +324,19 @@ __global__ __launch_bounds__(256, 1) void gemm_wave_kernel(const uint16_t *__res
   const int KF = K >> 4, MF = (M + 31) >> 5, NF = N >> 5;
   const int KC_all = KF / 2;                    // 32-column chunks
   // Work items are (K range, tile) pairs, K range major, dealt XCD-contiguously as in
-  // gemm_tile_kernel.  Tiles run through groups of 4 row tiles, row tile fastest: the 32
-  // workgroups resident on one XCD then cover a block of about 4 x 8 tiles and re-read each
-  // other's A and W slices in its L2 (at 4096 rows the loads alone take 2600 us for the 8B
-  // LM head, against 2940 us with all 16 row tiles first).
+  // gemm_tile_kernel, row tile fastest.  From 16 row tiles on they run through groups of 4 row
+  // tiles: the 32 workgroups resident on one XCD then cover a block of about 4 x 8 tiles and
+  // re-read each other's A and W slices in its L2 (calls of 4 layers at the 8B widths: 8210 rows
+  // 15.4 -> 14.9 ms, 4108 rows 8.03 -> 7.98).  With fewer row tiles a ragged last group costs
+  // more than that brings (1279 rows 3.69 -> 3.59 ms without groups, 1512 rows 2.84 -> 2.80;
+  // 2060 rows the same).
   const int v = (int)(blockIdx.x % 8u) * per_xcd + (int)(blockIdx.x / 8u);
   const int splits = (KC_all + kc_split - 1) / kc_split;
   if (v >= tiles * splits) return;
   const int z = v / tiles, t = v % tiles;
-  constexpr int GM = 4;
+  const int gm = tiles_m >= 16 ? 4 : tiles_m;
   const int tiles_n = tiles / tiles_m;
-  const int g0 = t / (GM * tiles_n) * GM, gr = min(GM, tiles_m - g0), tg = t - g0 * tiles_n;
+  const int g0 = t / (gm * tiles_n) * gm, gr = min(gm, tiles_m - g0), tg = t - g0 * tiles_n;
   const int tm = g0 + tg % gr, tn = tg / gr;
   const int kc0 = z * kc_split;
   const int KC = min(KC_all, kc0 + kc_split) - kc0;

@@ -9,15 +9,14 @@
   NULL);
 * more than 256 rows (24 requests x 17 rows = 408) and 2108 rows (124 x 17), which the
   LDS-staged tile GEMM serves in two and nine rows of 256 x 256 tiles;
-* 129-256 rows, where the 32-column weight-ring GEMM runs 8 waves on two row halves: an
-  odd number of 32-row fragments (150 rows: one half carries a zero fragment) and an even
-  one (192 rows);
+* 150 and 192 rows, the 192-row tile partly and wholly filled;
 * an out-of-range block id in the page table: the kernels clamp it, write nothing through
   it, and wisp_check reports a device input error;
 * a bf16 model of odd widths: d_model 96, d_ff 160, 3 query heads on 1 kv head, vocabulary
-  1056.  Every projection then has a partly filled last column tile and a K shorter than
-  one weight ring, and the GQA group is not a power of two; at 34 rows (weight ring) and
-  612 rows (256 x 256 tiles, most columns of the narrow projections past the edge).
+  1056.  Every projection then has a partly filled last column tile and a K of a few
+  chunks, and the GQA group is not a power of two; at 34 rows (the weight ring where K is no
+  multiple of 64, 64-row tiles elsewhere), 192 rows (192-row tiles) and 612 rows (256 x 256
+  tiles, most columns of the narrow projections past the edge).
 """
 import numpy as np
 import pytest
@@ -133,18 +132,16 @@ def test_2108_rows_in_lds_staged_tiles():
 
 @pytest.mark.parametrize("B,gamma", [(10, 14), (12, 15)], ids=["150rows", "192rows"])
 def test_rows_around_the_ring_to_tile_switch(B, gamma):
-    """150 rows (5 fragments) and 192 rows (6): the 192-row LDS-staged tile with its K split,
-    partly and wholly filled (the paired-wave weight ring at these row counts is covered by
-    the odd-width model at 192 rows)."""
+    """150 rows (5 fragments) and 192 rows (6): the 192-row LDS-staged tile, partly and wholly
+    filled."""
     ctx = [int(c) for c in np.random.default_rng(B).integers(0, 80, size=B)]
     _run_case(MINI_BF16, ctx, [gamma] * B, _bf16_abs)
 
 
 def test_odd_widths_bf16_at_192_rows():
-    """The odd-width model at 192 rows: the projections whose K is an odd multiple of 32
-    (QKV, gate/up and the LM head over d_model 96, down over d_ff 160) keep the paired-wave
-    weight ring at 6 fragments; the output projection (K = 192) runs the 192-row tile on a
-    partly filled column tile."""
+    """The odd-width model at 192 rows: 192-row tiles of 128 columns, the last of each output
+    partly filled, over K of 3 (d_model 96), 5 (d_ff 160) and 6 chunks of 32 (the output
+    projection)."""
     B = 12
     ctx = [int(c) for c in np.random.default_rng(8).integers(0, 60, size=B)]
     _run_case(ODD_BF16, ctx, [15] * B, _bf16_abs)

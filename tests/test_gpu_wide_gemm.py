@@ -6,12 +6,12 @@ in seconds: d_model 512, 8 query heads on 2 kv heads of 64, d_ff 8192 (gate/up 1
 columns), vocabulary 65536 (wide enough for the LM head's own plan), bf16, 2 layers.
 
 Cases: 14 rows (gate/up on 64 x 128 tiles in one K range with the SwiGLU epilogue, the LM
-head on 32 x 256 tiles with the row-maxima epilogue, the narrower projections on the
-weight ring), 44 rows (the LM head on the 64-column weight ring, the rest on 64 x 128
-tiles), 153 rows (the LM head on the 64-column weight ring, the rest on 192-row tiles,
-gate/up in one K range with SwiGLU in its epilogue), 476 and 680 rows (every projection on
-256 x 256 tiles, gate/up with two K ranges at 476 rows and with SwiGLU in its epilogue at
-680, the narrow ones with K split).  Checks: logits within 2e-2 max-abs of the oracle, every written K/V value within
+head on 32 x 256 tiles, the narrower projections on the weight ring), 44 rows (the LM head on
+the 64-column weight ring, the rest on 64 x 128 tiles), 153 rows (the LM head on the
+64-column weight ring, the rest on 192-row tiles, gate/up in one K range with SwiGLU in its
+epilogue), 476 and 680 rows (256 x 256 tiles, down on 192-row tiles; gate/up with two K
+ranges at 476 rows and with SwiGLU in its epilogue at 680, the narrow ones with K split).
+Checks: logits within 2e-2 max-abs of the oracle, every written K/V value within
 max(two bf16 ulps at its head vector's scale, twice the oracle's floor of its layer),
 untouched slots bit-identical, decisions on the GPU's own logits bit-exact except flagged
 near-ties.
