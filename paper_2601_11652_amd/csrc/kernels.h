@@ -117,8 +117,7 @@ constexpr int kAttnWindowPages = 64;   // pages whose block ids a wave holds (on
 constexpr int kAttnCombineChunks = 8;  // partials the combine loads per round of dependent loads
 
 // split-KV partials of every item (wave w runs items first[w] .. first[w + 1] - 1, or item w if
-// first is null), then their
-// fixed-order combine into `out`
+// first is null), then their fixed-order combine into `out`
 void attention_bf16_main(const StepDesc &d, const AttnItem *items, const int32_t *first, int n_waves, int item_rows,
                          const uint16_t *q, const uint16_t *k_pool, const uint16_t *v_pool, float *part_o,
                          float *part_ml, uint16_t *out, bool out_packed, int out_K, int nq, int nkv, int hd,
