@@ -234,9 +234,10 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
   // A way to give every item a wave of its own: its items' pairs and its estimated time (us),
   // the longer of a wave's chain of pairs (starting takes as long as 6, or beside a second wave
   // 10, 7 at head_dim 64) and of the K and V from memory (pairs that another row group reads too
-  // count 0.3 or, with two waves per SIMD, 0.6), and the combine, 4 us up to 8 items of a group
-  // and 5 + 0.18 per item beyond.  (1 request of 30k, 32 rows: 66 us with items of 12 pairs, 48
-  // with 20, 52 with 32.  4 of 0.5-4k, 8 query heads per kv head: 27 us with 32 rows, 38 with
+  // count 0.3 or, with two waves per SIMD, 0.6), and the combine, 4 us up to 8 items of a group,
+  // beyond it 4.9 + 0.18 per item and the partials at 6 TB/s (8 of 0.5-2k, 4 heads per kv head:
+  // 23 us in 952 items of 3 pairs, 21 in 376 of 8).  (1 request of 30k, 32 rows: 66 us with
+  // items of 12 pairs, 48 with 20, 52 with 32.  4 of 0.5-4k, 8 query heads per kv head: 27 us with 32 rows, 38 with
   // 48, 46 with 64.  32 of 0.5-2k, 4 heads: 37 us in 944 items of 12 pairs, 46 in 1900 of 6, two
   // waves per SIMD; at head_dim 64, 16 heads on 16, 35 in 1000 of 24, 32 in 1888 of 10.  12 of
   // 2-6k, 16 heads on 16: 91 in 1000 of 24, 72 in 1900 of 13.  22 of 3-4.5k and 28-40 rows: 90
@@ -248,6 +249,7 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
     int64_t L = 0;   // 0: none
     double us = 1e30;
   };
+  auto partials = [&](int64_t n, int rows) { return (double)n * rows * (p.hd + 2) * 4 / 6e6; };
   // the shortest items of at most L1 pairs that one wave (two) per SIMD cover, or, with one,
   // longer ones that take less (fewer than two per SIMD would leave loads unissued)
   auto try_items = [&](Items &best, int r, bool two, int64_t L1) {
@@ -257,7 +259,8 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
     for (int64_t l = shortest(2, L1, two ? 2 * slots : slots); l && l <= kAttnWindowPages / 2; ++l) {
       const int64_t n = (c->most + l - 1) / l;
       const double chain = two ? (l + (hd64 ? 7 : 10)) * kChain[hd64][r] * kTwo[hd64] : (l + 6) * kChain[hd64][r];
-      const double t = std::max(chain, mem) + (n <= kAttnCombineChunks ? 4.0 : 5.0 + 0.18 * n);
+      const double t = std::max(chain, mem) +
+                       (n <= kAttnCombineChunks ? 4.0 : 4.9 + 0.18 * n + partials(count_items(l), kRows[r]));
       if (t < best.us) best = Items{r, l, t};
       if (two) break;
     }
@@ -286,7 +289,9 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
   } else {
     // Items of up to 32 pairs where one wave per SIMD covers them, or of up to 16 (24 with 48 rows)
     // where two do and have room; equal shares of all pairs per wave where that is estimated to
-    // take less (its pairs at the rate of kStream and 20 us, 12 at head_dim 64), and beyond.
+    // take less (its pairs at the rate of kStream and 20 us, 12 at head_dim 64, and half of the
+    // partials where a group has more than 8: the other half is in the rate), and beyond.  (40 of
+    // 0.2-16k: 95 us in 1016 items, 114 in shares; 4 of 10-30k, 8 heads: 84 and 76.)
     // (256 of 1-8k, 110 pairs per wave: 610 us in shares, 692 in items; 48 rows, 64 of 0.5-4k:
     // 90, against 118 in 1040 items; 22 of 3-4.5k 66, against 63 in 912 items of 24 pairs.)
     // Where the row groups alone outnumber the waves, items of up to 16 pairs, dispatched as
@@ -296,7 +301,11 @@ wisp_status plan_attention(Plan &p, const wisp_batch_desc *d, const std::vector<
     const bool two = kRows[best] == 32 || (hd64 && kRows[best] == 48);   // waves per SIMD of shares
     waves = two ? 2 * slots : slots;
     Items a;
-    if (cand[best].total > kShort * waves) a.us = p.nkv * cand[best].us * 1e-3 + (hd64 ? 12.0 : 20.0);
+    if (cand[best].total > kShort * waves) {
+      a.us = p.nkv * cand[best].us * 1e-3 + (hd64 ? 12.0 : 20.0);
+      if (cand[best].most * waves > kAttnCombineChunks * cand[best].total)
+        a.us += 0.5 * partials(waves + p.nkv * (int64_t)cand[best].pairs.size(), kRows[best]);
+    }
     for (int r = 0; r < 3; ++r) try_items(a, r, false, 2 * kShort);
     try_items(a, 0, true, kShort);
     if (hd64) try_items(a, 1, true, 24);

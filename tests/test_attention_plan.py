@@ -78,6 +78,8 @@ def test_one_request_of_more_than_65536_row_groups():
     (64, 8, 128, [500, 900, 2000, 4000], [2, 8, 5, 1], None, 32, False),
     (32, 2, 128, [1200], [8], None, 32, False),
     (64, 8, 64, [2000, 8000], [8, 8], None, 32, False),
+    # and up to 8 of them per group where more would have many partials
+    (32, 8, 128, [600 + 190 * k for k in range(8)], [1 + k for k in range(8)], None, 32, False),
     # long contexts of few requests: more items per group than one round of the combine
     (32, 8, 128, [30000], [8], None, 32, False),
     # prompts: 32-row items, dispatched in turn
@@ -93,6 +95,8 @@ def test_choices(n_q, n_kv, hd, ctx, gamma, prefill, rows, shares):
     assert (p["rows"], p["shares"]) == (rows, shares), (p["rows"], p["shares"], p["waves"])
     if len(ctx) == 1 and ctx[0] == 30000:
         assert p["most"] > 8 and p["waves"] <= 1024
+    if len(ctx) == 8:
+        assert p["most"] <= 8, p["most"]
 
 
 def test_gpu_cases_take_the_plan_they_are_written_for():
