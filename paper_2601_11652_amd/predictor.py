@@ -17,7 +17,7 @@ import os
 import sys
 
 
-from . import RejectMLP, wisp_draft_stats, wisp_reject_predict
+from . import RejectMLP, lib, wisp_draft_stats, wisp_reject_predict, workspace
 from .records import command_line
 
 HBM_PEAK_GBS = 8000.0
@@ -44,7 +44,8 @@ def bench_stats(rows: int, vocab: int) -> dict:
     g.manual_seed(rows * 7 + vocab)
     x = torch.randn(rows, vocab, generator=g, device="cuda") * 2.0
     st = torch.empty(rows, 4, device="cuda")
-    ms = _time(lambda: wisp_draft_stats(x, vocab, 1.0, st))
+    ws = workspace(lib.wisp_draft_stats_workspace_size(rows, vocab))
+    ms = _time(lambda: wisp_draft_stats(x, vocab, 1.0, st, ws))
     nbytes = rows * (vocab * 4 + 16)
     gbs = nbytes / (ms / 1e3) / 1e9
     return {"rows": rows, "vocab": vocab, "us": ms * 1e3, "bytes": nbytes, "GBs": gbs, "frac": gbs / HBM_PEAK_GBS}
