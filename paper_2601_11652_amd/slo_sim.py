@@ -434,8 +434,8 @@ def report(rec: dict, replay: dict | None = None) -> str:
     if rec.get("robustness"):
         L.append("")
         L.append("Estimator error (Sec. 4.4's guard time): the SLO policy with lost deadlines out of the critical "
-                 "queue estimates with the linear fit while batches take the roofline-shaped fit's time (a "
-                 "different, better model of this GPU), times the same lognormal error. Response violation % : "
+                 "queue estimates with the linear fit while batches take the roofline-shaped fit's time (the "
+                 "same model where the fitted knot is 0), times the same lognormal error. Response violation % : "
                  "late verification % per class:\n")
         L.append("| N | guard (ms) | 2 tok/s | 4 tok/s | 6 tok/s | 8 tok/s | goodput | mean batch |")
         L.append("|---|---|---|---|---|---|---|---|")
